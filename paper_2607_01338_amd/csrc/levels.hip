@@ -4,11 +4,13 @@
 // Balance"; "Spectral-Line Configuration"; "Grid Precomputation").
 //
 // Host side: a reader of molecular data in the LAMDA .dat convention.
-// Device side: one wavefront per grid node (ln n_H2, chi, ln T) assembles the
-// rate matrix of every level in LDS and solves the balance, with the ground
-// state's equation replaced by the conservation row, by FP64 Gaussian
-// elimination with partial pivoting (lane j holds column j, the right-hand
-// side is column L). The node keeps the observed transition's population
+// Device side: one wavefront per grid node (ln n_H2, chi, ln T) solves the
+// balance in FP64 by state reduction (Grassmann, Taksar and Heyman, "Regenerative
+// Analysis and Steady State Distributions for Markov Chains", 1985) on the rate
+// matrix held in registers. A node that cannot be reduced (a level with no
+// way down to the levels before it) is left to a second kernel, which replaces
+// the ground state's equation by the conservation row and eliminates with
+// partial pivoting in LDS. The node keeps the observed transition's population
 // factors FU = (g_l/g_u) f_u and FL = f_l - FU as an FP32 pair.
 
 #include <hip/hip_runtime.h>
@@ -21,6 +23,7 @@
 #include <string>
 #include <vector>
 
+#include "device_util.h"
 #include "host_common.h"
 
 using namespace iris::host;
@@ -74,14 +77,166 @@ struct LevelsParams {
   int n_n, n_c, n_t;
   double lnn0, dlnn, chi0, dchi, lnt0, dlnt;
   float2* grid;
+  int* unreduced;  // nodes left to the pivoting kernel (zero at launch)
+  int splits;      // workgroups that share the densities of one (chi, T)
 };
 
+// Interval and weight of T in partner p's tabulated temperatures, the end
+// values held beyond them.
+__device__ __forceinline__ void coll_temp(const LevelsParams& P, int p, double T, int& k,
+                                          double& w) {
+  const double* tt = P.temps + P.temp_off[p];
+  const int nt = P.n_temp[p];
+  k = 0;
+  w = 0.0;
+  if (T >= tt[nt - 1]) {
+    k = nt - 1;
+  } else if (T > tt[0]) {
+    while (tt[k + 1] <= T) ++k;
+    w = (T - tt[k]) / (tt[k + 1] - tt[k]);
+  }
+}
+
+__device__ __forceinline__ double read_lane(double x, int i) {
+  const uint64_t u = (uint64_t)__double_as_longlong(x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, i);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), i);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// f(N), f(N - 1), .., f(1), each N a compile-time constant.
+template <int N, typename F>
+__device__ __forceinline__ void unroll_down(F&& f) {
+  f(std::integral_constant<int, N>{});
+  if constexpr (N > 1) unroll_down<N - 1>(f);
+}
+
+// Wavefronts of a reduction workgroup; they share one (chi, T).
+constexpr int kOtWaves = 4;
+
+// State reduction of the level balance. The stationary populations of a chain
+// with rates q[i][j] (i -> j) need only its off-diagonal rates: eliminating
+// the last state n adds q[i][n] q[n][j] / s_n, s_n = sum_{j<n} q[n][j], to
+// every q[i][j], i, j < n; then pi_0 = 1, pi_n = (sum_{i<n} pi_i q[i][n]) / s_n.
+// Nothing is subtracted, so no pivoting is needed and every population keeps
+// its relative accuracy.
+//
+// Lane j holds column j (q[i] = rate i -> j) in registers, NL >= L rows with
+// all loops unrolled; column n goes out as scalars by lane reads. Bound by
+// VALU issue: two lane reads and one FP64 FMA per (n, i), L^2 / 2 of them, on
+// columns that shrink from L lanes to 1. The densities of one (chi, T) share
+// the collision sums, which are linear in n_H2: a workgroup builds
+// q = base + n_H2 coll in LDS once for all of its nodes. 128 x 64 x 64 nodes
+// of 41 levels: 67.5 ms as one LDS elimination with pivoting per node (32 KB
+// of LDS a wavefront, every rate and its detailed-balance exponential per
+// node), 4.4 ms like this.
+template <int NL>
+__global__ __launch_bounds__(64 * kOtWaves)
+__attribute__((amdgpu_waves_per_eu(NL <= 48 ? 4 : 3))) void ot_reduce_kernel(const LevelsParams P) {
+  // Rates i -> j, rows and columns beyond L zero: radiative, and collisional
+  // per n_H2.
+  __shared__ double base[NL * NL], coll[NL * NL];
+  const int L = P.L;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int pair = blockIdx.x / P.splits, split = blockIdx.x % P.splits;
+  const int i_t = pair % P.n_t, i_c = pair / P.n_t;
+  const double chi = P.chi0 + i_c * P.dchi;
+  const double T = exp(P.lnt0 + i_t * P.dlnt);
+  for (int i = threadIdx.x; i < NL * NL; i += blockDim.x) base[i] = coll[i] = 0.0;
+  __syncthreads();
+  for (int t = threadIdx.x; t < P.n_rad; t += blockDim.x) {
+    const int u = P.rad_u[t], l = P.rad_l[t];
+    const double A = P.rad_a[t], nb = P.rad_nbar[t];
+    atomicAdd(&base[u * NL + l], A * (1.0 + nb));
+    atomicAdd(&base[l * NL + u], P.g[u] / P.g[l] * A * nb);
+  }
+  // Collisions, partner by partner (a partner lists each pair once, or once
+  // each way round).
+  for (int p = 0; p < P.n_part; ++p) {
+    const double share = P.dens_a[p] + P.dens_b[p] / chi;
+    int k;
+    double w;
+    coll_temp(P, p, T, k, w);
+    for (int c = threadIdx.x; c < P.n_coll[p]; c += blockDim.x) {
+      const int u = P.coll_u[P.coll_off[p] + c], l = P.coll_l[P.coll_off[p] + c];
+      const double* r = P.rates + P.rate_off[p] + (long)c * P.n_temp[p];
+      const double kul = w == 0.0 ? r[k] : r[k] + w * (r[k + 1] - r[k]);
+      const double down = kul * share;
+      atomicAdd(&coll[u * NL + l], down);
+      atomicAdd(&coll[l * NL + u], down * (P.g[u] / P.g[l]) * exp(-(P.E[u] - P.E[l]) / T));
+    }
+    __syncthreads();
+  }
+  __syncthreads();  // also where there are no partners
+
+  const int n_lo = (int)((long)P.n_n * split / P.splits);
+  const int n_hi = (int)((long)P.n_n * (split + 1) / P.splits);
+  for (int i_n = n_lo + wave; i_n < n_hi; i_n += kOtWaves) {
+    const double nh2 = exp(P.lnn0 + i_n * P.dlnn);
+    double q[NL];
+    const int col = lane < NL ? lane : 0;  // columns beyond L are never read
+#pragma unroll
+    for (int i = 0; i < NL; ++i) q[i] = fma(nh2, coll[i * NL + col], base[i * NL + col]);
+    double inv = 1.0;  // lane n: 1 / s_n
+    bool bad = false;
+    // Recomputed per node and step: hoisted out of the loops, the lane masks of
+    // every step would not fit the scalar registers.
+    int ln = lane, nl = L;
+    asm volatile("" : "+v"(ln), "+s"(nl));
+    unroll_down<NL - 1>([&](auto step) {
+      constexpr int n = decltype(step)::value;
+      if (n < nl) {
+        const double row = ln < n ? q[n] : 0.0;
+        const double s = read_lane(group_scan_dpp<64>(row), 63);
+        if (!(s > 0.0)) bad = true;
+        const double is = 1.0 / s;
+        if (ln == n) inv = is;
+        const double f = row * is;
+#pragma unroll
+        for (int i = 0; i < n; ++i) q[i] = fma(read_lane(q[i], n), f, q[i]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    });
+    // pi_n in lane n: acc collects sum_i pi_i q[i][n].
+    int iu = P.u_obs, il = P.l_obs;
+    asm volatile("" : "+s"(iu), "+s"(il));
+    double acc = 0.0, p = 1.0, tot = 1.0;
+    double pu = iu == 0 ? 1.0 : 0.0, pl = il == 0 ? 1.0 : 0.0;
+    unroll_down<NL - 1>([&](auto step) {
+      constexpr int n = NL - decltype(step)::value;
+      if (n < nl) {
+        acc = fma(p, q[n - 1], acc);
+        p = read_lane(acc * inv, n);
+        tot += p;
+        if (iu == n) pu = p;
+        if (il == n) pl = p;
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    });
+    if (!(tot < 1e300)) bad = true;  // also NaN
+    if (lane == 0) {
+      const double fu = pu / tot, fl = pl / tot;
+      const double FU = P.g[P.l_obs] / P.g[P.u_obs] * fu;
+      const long pt = ((long)i_c * P.n_t + i_t) * P.n_n + i_n;
+      P.grid[pt] = bad ? make_float2(__builtin_nanf(""), 0.f)
+                       : make_float2((float)FU, (float)(fl - FU));
+      if (bad) atomicAdd(P.unreduced, 1);
+    }
+  }
+}
+
+// Pivoting elimination of the nodes that the state reduction left (their
+// stored FU is NaN), one wavefront each: lane j holds column j of the balance
+// in LDS, the right-hand side is column L.
 __global__ __launch_bounds__(64) void ot_levels_kernel(const LevelsParams P) {
   __shared__ double M[kMaxLevels][64];
   const int lane = threadIdx.x;
   const int L = P.L;
   const int n_pts = P.n_n * P.n_c * P.n_t;
+  if (gload(P.unreduced) == 0) return;
   for (int pt = blockIdx.x; pt < n_pts; pt += gridDim.x) {
+    const float left = gload((const float*)(P.grid + pt));
+    if (left == left) continue;
     const int i_n = pt % P.n_n;
     const int i_t = (pt / P.n_n) % P.n_t;
     const int i_c = pt / (P.n_n * P.n_t);
@@ -102,16 +257,10 @@ __global__ __launch_bounds__(64) void ot_levels_kernel(const LevelsParams P) {
     // Collisions, partner by partner (a partner lists each pair once).
     for (int p = 0; p < P.n_part; ++p) {
       const double ns = nh2 * (P.dens_a[p] + P.dens_b[p] / chi);
-      const double* tt = P.temps + P.temp_off[p];
       const int nt = P.n_temp[p];
-      int k = 0;
-      double w = 0.0;
-      if (T >= tt[nt - 1]) {
-        k = nt - 1;
-      } else if (T > tt[0]) {
-        while (tt[k + 1] <= T) ++k;
-        w = (T - tt[k]) / (tt[k + 1] - tt[k]);
-      }
+      int k;
+      double w;
+      coll_temp(P, p, T, k, w);
       for (int c = lane; c < P.n_coll[p]; c += 64) {
         const int u = P.coll_u[P.coll_off[p] + c], l = P.coll_l[P.coll_off[p] + c];
         const double* r = P.rates + P.rate_off[p] + (long)c * nt;
@@ -178,6 +327,16 @@ __global__ __launch_bounds__(64) void ot_levels_kernel(const LevelsParams P) {
       P.grid[pt] = make_float2((float)FU, (float)(fl - FU));
     }
   }
+}
+
+// The reduction compiled for the smallest multiple of 8 rows that holds L.
+template <int NL>
+int launch_ot_reduce(const LevelsParams& P, int blocks, hipStream_t st) {
+  if constexpr (NL > 8)
+    if (P.L <= NL - 8) return launch_ot_reduce<NL - 8>(P, blocks, st);
+  hipLaunchKernelGGL((ot_reduce_kernel<(NL < kMaxLevels ? NL : kMaxLevels)>), dim3(blocks),
+                     dim3(64 * kOtWaves), 0, st, P);
+  return (int)hipGetLastError();
 }
 
 }  // namespace iris
@@ -413,7 +572,7 @@ iris_status iris_levels_create(const iris_molecule* mol, const iris_levels_confi
   const size_t oE = carve(L * 8), oG = carve(L * 8), oRu = carve(nr * 4), oRl = carve(nr * 4),
                oRa = carve(nr * 8), oRn = carve(nr * 8), oCu = carve(cu.size() * 4 + 4),
                oCl = carve(cl.size() * 4 + 4), oT = carve(temps.size() * 8 + 8),
-               oR = carve(rates.size() * 8 + 8);
+               oR = carve(rates.size() * 8 + 8), oB = carve(4);
   std::vector<char> host(off, 0);
   std::memcpy(host.data() + oE, mol->energy_k.data(), L * 8);
   std::memcpy(host.data() + oG, mol->g.data(), L * 8);
@@ -467,9 +626,18 @@ iris_status iris_levels_create(const iris_molecule* mol, const iris_levels_confi
   P.lnt0 = std::log(cfg->t_lo_k);
   P.dlnt = cfg->n_t > 1 ? (std::log(cfg->t_hi_k) - std::log(cfg->t_lo_k)) / (cfg->n_t - 1) : 0.0;
   P.grid = lv->grid;
-  const int blocks = (int)std::min<long>(n_pts, 16384);
-  hipLaunchKernelGGL(iris::ot_levels_kernel, dim3(blocks), dim3(64), 0, (hipStream_t)stream, P);
-  e = (int)hipGetLastError();
+  P.unreduced = (int*)(base + oB);  // zeroed with the tables
+  // One workgroup per (chi, T), more where that leaves the GPU short of work
+  // (its densities then split over several, four nodes at least each).
+  const long pairs = (long)cfg->n_chi * cfg->n_t;
+  P.splits = (int)std::max<long>(
+      1, std::min<long>((cfg->n_n + iris::kOtWaves - 1) / iris::kOtWaves, 4096 / pairs));
+  e = iris::launch_ot_reduce<64>(P, (int)(pairs * P.splits), (hipStream_t)stream);
+  if (!e) {
+    const int blocks = (int)std::min<long>(n_pts, 2048);
+    hipLaunchKernelGGL(iris::ot_levels_kernel, dim3(blocks), dim3(64), 0, (hipStream_t)stream, P);
+    e = (int)hipGetLastError();
+  }
   if (e) {
     iris_levels_destroy(lv);
     return hip_status(e, "levels kernel");

@@ -72,6 +72,40 @@ def test_grid_of_the_golden_three_level_molecule(transition, t_bar):
     lv.close()
 
 
+@pytest.mark.parametrize("n_levels", [2, 8, 9, 24, 25, 41, 48, 49, 63])
+def test_grid_at_the_edges_of_the_compiled_sizes(n_levels, tmp_path):
+    # The reduction is compiled for 8, 16, .., 56, 63 rows; densities that do
+    # not divide among a workgroup's wavefronts, one and several per workgroup.
+    path = str(tmp_path / "rotor.dat")
+    W.write_lamda(path, W.synthetic_rotor_molecule(n_levels=n_levels, seed=n_levels))
+    cfg = dict(n_n=5, n_chi=2, n_t=3, ln_nh2_lo=-2.0, ln_nh2_hi=16.0, chi_lo=0.3, chi_hi=1.0,
+               t_lo_k=4.0, t_hi_k=900.0)
+    transition = 1 if n_levels == 2 else 2
+    say(f"[levels] rotor of {n_levels} levels")
+    lv = rt.Levels(rt.Molecule(path), transition, **cfg)
+    assert_grid_close(lv.grid(), oracle_grid(Lv.read_lamda(path), cfg, transition), "rotor")
+    lv.close()
+
+
+def test_grid_of_a_chain_that_cannot_be_reduced(tmp_path):
+    # Nothing but spontaneous decay to a ground state listed last: the state
+    # reduction has no way down from it, and the pivoting elimination answers.
+    mol = W.Molecule(name="ground last", weight_amu=29.0, energy_cm=np.array([20.0, 8.0, 0.0]),
+                     g=np.array([5.0, 3.0, 1.0]), qn=["2", "1", "0"], rad_up=np.array([0, 1]),
+                     rad_low=np.array([1, 2]), a_ul=np.array([2e-6, 1e-6]),
+                     freq_ghz=np.array([359.75, 239.83]), partners=[])
+    path = str(tmp_path / "last.dat")
+    W.write_lamda(path, mol)
+    cfg = dict(n_n=3, n_chi=1, n_t=2, ln_nh2_lo=0.0, ln_nh2_hi=9.0, chi_lo=1.0, chi_hi=1.0,
+               t_lo_k=5.0, t_hi_k=50.0)
+    say("[levels] ground state listed last, decay only")
+    lv = rt.Levels(rt.Molecule(path), 2, t_bar_k=0.0, **cfg)
+    ref = oracle_grid(Lv.read_lamda(path), cfg, 2, 0.0)  # everything in the ground state
+    for a, b in zip(lv.grid(), (ref.FU, ref.FL)):
+        assert np.max(np.abs(a - b)) <= 2e-6
+    lv.close()
+
+
 def test_paper_size_grid_sampled_nodes(rotor):
     # (n_rho, n_chi, n_T) = (128, 64, 64) as in the paper's study, 41 levels.
     _, mol, cmol = rotor
