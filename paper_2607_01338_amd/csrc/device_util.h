@@ -110,7 +110,7 @@ struct ItemClaim {
       const int n = begin[x + 1] - begin[x];
       const int tail = n - static_items(n);
       int k = tail;
-      if (tail > 0 && (threadIdx.x & 63) == 0) k = atomicAdd(&counter[x], 1);
+      if (tail > 0 && (threadIdx.x & 63) == 0) k = atomicAdd(&counter[x * kHeadStride], 1);
       k = __builtin_amdgcn_readfirstlane(k);
       if (k < tail) return begin[x] + (n - tail) + k;
       ++tried;

@@ -123,6 +123,9 @@ struct WorkItem {
 // sightlines, which share cache lines of the native field layout, are
 // handled under one L2.
 constexpr int kSlices = 8;
+// Ints between the heads of two slices: each in a 128-byte line of its own, so
+// that the XCDs' claims do not queue up behind each other in one line.
+constexpr int kHeadStride = 32;
 
 struct PlanFwdParams {
   const FwdParams* cubes;  // device array, one per cube
@@ -130,7 +133,7 @@ struct PlanFwdParams {
   int32_t slice_begin[kSlices + 1];
   int32_t wave_floats;     // LDS floats per wavefront (max over the cubes)
   int32_t static_rounds;   // 1: the launch runs alone with every workgroup resident
-  int* counter;            // kSlices queue heads, zeroed before each launch
+  int* counter;            // kSlices queue heads, kHeadStride apart, zeroed before each launch
 };
 
 struct AdjParams {
@@ -182,7 +185,7 @@ struct PlanAdjParams {
   int32_t slice_begin[kSlices + 1];
   int32_t wave_floats;
   int32_t static_rounds;   // 1: the launch runs alone with every workgroup resident
-  int* counter;            // kSlices queue heads
+  int* counter;            // kSlices queue heads, kHeadStride apart
 };
 
 struct LayoutParams {

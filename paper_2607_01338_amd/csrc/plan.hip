@@ -386,7 +386,7 @@ iris_status build_plan(const iris_cube* cubes, int n, const iris_line* L, int fl
   //    where used).
   Carver cv;
   const size_t o_tab = cv.take(kTabBytes);
-  const size_t o_ctr = cv.take((3 + (size_t)n_acl) * kSlices * sizeof(int));
+  const size_t o_ctr = cv.take((3 + (size_t)n_acl) * kSlices * kHeadStride * sizeof(int));
   const size_t o_fwd = cv.take((size_t)n * sizeof(FwdParams));
   const size_t o_adj = adj ? cv.take((size_t)n * sizeof(AdjParams)) : 0;
   size_t o_fq[3];
@@ -406,7 +406,7 @@ iris_status build_plan(const iris_cube* cubes, int n, const iris_line* L, int fl
   }
   char* base = (char*)P->mem;
   const void* tab = base + o_tab;
-  // [3 + n_acl][kSlices]: forward packings 1, 2, 4, then the adjoint classes.
+  // [3 + n_acl][kSlices], kHeadStride apart: forward packings 1, 2, 4, then the adjoint classes.
   int* counters = (int*)(base + o_ctr);
 
   // 5. Per-cube kernel parameters.
@@ -530,7 +530,7 @@ iris_status build_plan(const iris_cube* cubes, int n, const iris_line* L, int fl
     qf[c].items = (const WorkItem*)(base + o_fq[c]);
     for (int x = 0; x <= kSlices; ++x) qf[c].slice_begin[x] = fq[c].begin[x];
     qf[c].wave_floats = fwd_wave_floats[c];
-    qf[c].counter = counters + c * kSlices;
+    qf[c].counter = counters + c * kSlices * kHeadStride;
     const int64_t resident =
         (int64_t)plan_forward_occupancy(fwd_wave_floats[c], kPackings[c], ck) * n_cu;
     const double share = fwork > 0.0 ? fq[c].work / fwork : 1.0;
@@ -554,7 +554,7 @@ iris_status build_plan(const iris_cube* cubes, int n, const iris_line* L, int fl
     qa[c].items = (const WorkItem*)(base + o_aq[c]);
     for (int x = 0; x <= kSlices; ++x) qa[c].slice_begin[x] = acl[c].q.begin[x];
     qa[c].wave_floats = acl[c].wave_floats;
-    qa[c].counter = counters + (3 + c) * kSlices;
+    qa[c].counter = counters + (3 + c) * kSlices * kHeadStride;
     const int64_t resident = (int64_t)acl[c].occupancy * n_cu;
     adj_blocks[c] = persistent_grid(resident, (int64_t)acl[c].q.items.size(), 1);
     // Items claimed one at a time: an adjoint item (a whole sightline's
@@ -588,8 +588,9 @@ iris_status build_plan(const iris_cube* cubes, int n, const iris_line* L, int fl
     int used[3], nb = 0;
     for (int c = 0; c < 3 && forward; ++c)
       if (fwd_blocks[c]) used[nb++] = c;
-    e = forward ? launch_zero_ints(counters, 3 * kSlices, P->cap)
-                : launch_zero_ints(counters + 3 * kSlices, n_acl * kSlices, P->cap);
+    e = forward ? launch_zero_ints(counters, 3 * kSlices * kHeadStride, P->cap)
+                : launch_zero_ints(counters + 3 * kSlices * kHeadStride,
+                                   n_acl * kSlices * kHeadStride, P->cap);
     if (forward && !e && ftiles)
       e = launch_batched_layout((const TransposeJob*)(base + o_fj), (int)fjobs.size(), ftiles,
                                 P->cap);
