@@ -3,12 +3,16 @@
 // sky axis (the l,v panels of the paper's figures). Cubes are FP32
 // [n1][n2][n_chan], channel fastest.
 //
-// The beam is separable: one pass along n2 into a workspace, one along n1 into
-// the output. A lane computes a run of four consecutive positions along the
-// pass axis for four channels (16-byte accesses when the rows allow it), so
-// that the 2R + 1 taps of the run share 4 + 2R loads; each XCD takes a
-// contiguous range of the work, so that rows re-read by neighbouring runs hit
-// in its L2. Both passes are bound by HBM: each reads and writes the cube once.
+// The beam is separable. Up to kBeamFusedRadius pixels one kernel does both
+// axes: it walks n1 row by row, convolves each row along n2 out of LDS and
+// keeps the 2R + 1 output rows it reaches in registers, so the cube is read
+// and written once. Wider beams, and an output that overlaps the cube, take
+// two passes, along n2 into a workspace and along n1 into the output: a lane
+// computes a run of four consecutive positions along the pass axis for four
+// channels (16-byte accesses when the rows allow it), so that the 2R + 1 taps
+// of the run share 4 + 2R loads; each XCD takes a contiguous range of the
+// work, so that rows re-read by neighbouring runs hit in its L2. Both ways are
+// bound by HBM and sum the taps in the same order (equal results).
 
 #include <hip/hip_runtime.h>
 
@@ -88,26 +92,149 @@ __global__ __launch_bounds__(256) void beam_pass_kernel(const BeamArgs a) {
   }
 }
 
-// Mean over sky axis `axis` of [n1][n2][C]: out [n_other][C], FP64 sums.
+// Both axes at once, R <= kBeamFusedRadius. A workgroup of nw wavefronts takes
+// 32 channels (lane % 32), 8 nw positions along n2 (a run of four per half
+// wavefront) and a segment of n1. Per row of n1 the 8 nw + 2R positions go to
+// LDS, the next row's loads already in flight; each lane convolves its run
+// along n2 (4 + 2R LDS reads for four outputs) and adds the result to the
+// 2R + 1 output rows in reach, held oldest first: the sum of row k moves down
+// to k - 1 in the multiply-add itself, so the window slides at no cost, and a
+// finished row leaves at the bottom. Positions outside the map count as zero.
+// Bound by HBM: 512 x 128 x 800, R = 5: two passes 320 us, this one 107 us
+// (0.42 GB; the halos, (1 + 2R/64)(1 + 2R/segment), come from L2).
+constexpr int kBeamFusedRadius = 12;
+constexpr int kBeamCh = 32;     // channels of a workgroup
+constexpr int kBeamPerWave = 8;  // positions along n2 per wavefront
+
+template <int R>
+__global__ __launch_bounds__(512) void beam_fused_kernel(const BeamArgs a, int seg_rows,
+                                                         int n_seg) {
+  constexpr int kTaps = 2 * R + 1;
+  extern __shared__ float rows[];  // [2][(positions + 2R)][kBeamCh]
+  const int nw = (int)(blockDim.x >> 6);
+  const int n1 = (int)a.n1, n2 = (int)a.n2, C = (int)a.C;
+  const int t2 = nw * kBeamPerWave;  // positions of the workgroup
+  const int held = t2 + 2 * R;       // with the halo
+  const int n_ch = (C + kBeamCh - 1) / kBeamCh;
+  // Channel blocks fastest: neighbouring workgroups share rows of the cube.
+  const int tile = xcd_tile((int)blockIdx.x, (int)gridDim.x);
+  const int cb = tile % n_ch, rest = tile / n_ch;
+  const int seg = rest % n_seg, p2_0 = rest / n_seg * t2;
+  const int lane = (int)(threadIdx.x & 63), wave = (int)(threadIdx.x >> 6);
+  const int ch = lane % kBeamCh, c = cb * kBeamCh + ch;
+  const bool in_c = c < C;
+  const int run = wave * kBeamPerWave + 4 * (lane / kBeamCh);  // first position of the lane's run
+  const int m0 = seg * seg_rows, m1 = min(m0 + seg_rows, n1);
+
+  float w[R + 1];
+#pragma unroll
+  for (int i = 0; i <= R; ++i) w[i] = a.w[i];
+  float acc[kTaps][4] = {};
+
+  // Loads of one row by the whole workgroup: position h of the halo tile and
+  // channel ch per lane, 2 nw positions per round.
+  constexpr int kRounds = (kBeamPerWave + 2 * R + 1) / 2;  // nw >= 1
+  float pre[kRounds];
+  const int h0 = (int)threadIdx.x / kBeamCh, hs = 2 * nw;
+  auto fetch = [&](int row) {
+#pragma unroll
+    for (int k = 0; k < kRounds; ++k) {
+      if (k * hs >= held) break;  // wider workgroups take fewer rounds
+      const int h = h0 + k * hs, p2 = p2_0 - R + h;
+      const bool in = h < held && in_c && p2 >= 0 && p2 < n2 && row >= 0 && row < n1;
+      pre[k] = in ? gload(a.in + ((int64_t)row * n2 + p2) * C + c) : 0.f;
+    }
+  };
+  fetch(m0 - R);
+  for (int row = m0 - R, b = 0; row < m1 + R; ++row, b ^= 1) {
+    float* buf = rows + b * held * kBeamCh;
+#pragma unroll
+    for (int k = 0; k < kRounds; ++k) {
+      if (k * hs >= held) break;
+      const int h = h0 + k * hs;
+      if (h < held) buf[h * kBeamCh + ch] = pre[k];
+    }
+    __syncthreads();  // also: the reads of this buffer two rows ago are done
+    if (row + 1 < m1 + R) fetch(row + 1);
+    float v[4] = {};
+#pragma unroll
+    for (int j = 0; j < 4 + 2 * R; ++j) {
+      const float x = buf[(run + j) * kBeamCh + ch];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const int d = j - R - m < 0 ? m + R - j : j - R - m;
+        if (d <= R) v[m] = fmaf(w[d], x, v[m]);
+      }
+    }
+    // acc[k] is output row row - R + k after the shift: distance |R - k|.
+#pragma unroll
+    for (int k = 0; k < kTaps; ++k) {
+      const float wk = w[k < R ? R - k : k - R];
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        acc[k][m] = fmaf(wk, v[m], k + 1 < kTaps ? acc[k + 1][m] : 0.f);
+    }
+    const int o = row - R;
+    if (o >= m0 && in_c) {
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        if (p2_0 + run + m < n2)
+          gstore(a.out + ((int64_t)o * n2 + p2_0 + run + m) * C + c, acc[0][m]);
+    }
+  }
+}
+
+// Workgroups of the fused kernel: the positions along n2 in equal tiles of at
+// most 64, and as many segments of n1 as stay resident together (four
+// wavefronts per SIMD up to R = 7, two beyond, by registers), none shorter
+// than twice the halo it re-reads.
+template <int R>
+int launch_beam_fused(const BeamArgs& a, hipStream_t st) {
+  if constexpr (R > 1)
+    if (a.R < R) return launch_beam_fused<R - 1>(a, st);
+  const int64_t tiles = (a.n2 + 63) / 64;
+  const int nw = (int)(((a.n2 + tiles - 1) / tiles + kBeamPerWave - 1) / kBeamPerWave);
+  const int64_t cols = tiles * ((a.C + kBeamCh - 1) / kBeamCh);
+  const int64_t resident = (R <= 7 ? 4096 : 2048) / nw;
+  const int64_t segs = std::max<int64_t>(1, std::min<int64_t>(resident / cols, a.n1 / (4 * R)));
+  const int seg_rows = (int)((a.n1 + segs - 1) / segs);
+  const int n_seg = (int)((a.n1 + seg_rows - 1) / seg_rows);
+  const size_t lds = (size_t)2 * (nw * kBeamPerWave + 2 * R) * kBeamCh * sizeof(float);
+  hipLaunchKernelGGL(beam_fused_kernel<R>, dim3((unsigned)(cols * n_seg)), dim3(64 * nw), lds, st,
+                     a, seg_rows, n_seg);
+  return (int)hipGetLastError();
+}
+
+// Mean over sky axis `axis` of [n1][n2][C]: out [n_other][C], FP64 sums. A
+// workgroup takes 64 columns (of V channels); its wavefronts each sum a
+// contiguous part of the axis, eight loads in flight, and the parts are added
+// in LDS. One lane per column left 400 to 1600 wavefronts waiting on one load
+// each (512 x 128 x 800 over n2: 74 us; like this 35 us).
+constexpr int kLvMaxParts = 16;
+
 template <int V>
-__global__ __launch_bounds__(256) void lv_mean_kernel(const float* cube, float* outp, int64_t n1,
-                                                      int64_t n2, int64_t C, int axis) {
+__global__ __launch_bounds__(64 * kLvMaxParts) void lv_mean_kernel(const float* cube, float* outp,
+                                                                   int64_t n1, int64_t n2,
+                                                                   int64_t C, int axis) {
   using T = typename std::conditional<V == 4, float4, float>::type;
+  __shared__ double part[kLvMaxParts][V][64];
   const int64_t nv = C / V;
   const int64_t n_other = axis == 0 ? n2 : n1;
   const int64_t n_axis = axis == 0 ? n1 : n2;
   const int64_t total = n_other * nv;
   const T* in = (const T*)cube;
   T* out = (T*)outp;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
+  const int lane = (int)(threadIdx.x & 63), p = (int)(threadIdx.x >> 6);
+  const int parts = (int)(blockDim.x >> 6);
+  const int64_t e = (int64_t)blockIdx.x * 64 + lane;
+  double acc[V] = {};
+  if (e < total) {
     const int64_t o = e / nv, k = e % nv;
     // Element (p1, p2, k) sits at (p1 n2 + p2) nv + k.
     const int64_t base = (axis == 0 ? o : o * n2) * nv + k;
     const int64_t step = (axis == 0 ? n2 : 1) * nv;
-    double acc[V] = {};
-    for (int64_t i = 0; i < n_axis; ++i) {
-      const T v = gload(in + base + i * step);
+    const int64_t lo = n_axis * p / parts, hi = n_axis * (p + 1) / parts;
+    auto add = [&](const T& v) {
       if constexpr (V == 4) {
         acc[0] += v.x;
         acc[1] += v.y;
@@ -116,19 +243,53 @@ __global__ __launch_bounds__(256) void lv_mean_kernel(const float* cube, float* 
       } else {
         acc[0] += v;
       }
+    };
+    constexpr int kU = 8;
+    int64_t i = lo;
+    for (; i + kU <= hi; i += kU) {
+      T v[kU];
+#pragma unroll
+      for (int u = 0; u < kU; ++u) v[u] = gload(in + base + (i + u) * step);
+#pragma unroll
+      for (int u = 0; u < kU; ++u) add(v[u]);
     }
-    const double s = 1.0 / (double)n_axis;
-    if constexpr (V == 4)
-      gstore(out + e, make_float4((float)(acc[0] * s), (float)(acc[1] * s), (float)(acc[2] * s),
-                                  (float)(acc[3] * s)));
-    else
-      gstore(out + e, (float)(acc[0] * s));
+    for (; i < hi; ++i) add(gload(in + base + i * step));
   }
+  if (parts > 1) {
+#pragma unroll
+    for (int m = 0; m < V; ++m) part[p][m][lane] = acc[m];
+    __syncthreads();
+    if (p) return;
+    for (int q = 1; q < parts; ++q)
+#pragma unroll
+      for (int m = 0; m < V; ++m) acc[m] += part[q][m][lane];
+  }
+  if (e >= total) return;
+  const double s = 1.0 / (double)n_axis;
+  if constexpr (V == 4)
+    gstore(out + e, make_float4((float)(acc[0] * s), (float)(acc[1] * s), (float)(acc[2] * s),
+                                (float)(acc[3] * s)));
+  else
+    gstore(out + e, (float)(acc[0] * s));
 }
 
-int grid_for(int64_t work) {
-  const int64_t b = (work + 255) / 256;
-  return (int)std::min<int64_t>(std::max<int64_t>(b, 1), 256 * 64);
+template <int V>
+int launch_lv_mean(const float* cube, float* out, int64_t n1, int64_t n2, int64_t C, int axis,
+                   hipStream_t st) {
+  const int64_t n_other = axis == 0 ? n2 : n1, n_axis = axis == 0 ? n1 : n2;
+  const int64_t blocks = (n_other * (C / V) + 63) / 64;
+  // Parts of the axis: enough wavefronts to fill the GPU (16 per CU), at least
+  // eight loads each.
+  int64_t parts = std::min<int64_t>((4096 + blocks - 1) / blocks, n_axis / 8);
+  parts = std::max<int64_t>(1, std::min<int64_t>(parts, kLvMaxParts));
+  hipLaunchKernelGGL(lv_mean_kernel<V>, dim3((unsigned)blocks), dim3((unsigned)(64 * parts)), 0, st,
+                     cube, out, n1, n2, C, axis);
+  return (int)hipGetLastError();
+}
+
+bool overlap(const void* a, const void* b, size_t bytes) {
+  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+  return x < y + bytes && y < x + bytes;
 }
 
 bool aligned4(const void* p, int64_t C) { return ((uintptr_t)p & 15) == 0 && (C & 3) == 0; }
@@ -183,6 +344,14 @@ iris_status iris_beam_convolve(const float* cube, float* out, int32_t n1, int32_
   }
   for (int i = 0; i <= a.R; ++i) a.w[i] = (float)(wd[i] / wsum);
   const hipStream_t st = (hipStream_t)stream;
+  // One kernel for both axes up to kBeamFusedRadius (its output rows in reach
+  // fill the registers beyond); it reads neighbours of what it writes, so an
+  // output that overlaps the cube takes the two passes.
+  if (a.R <= kBeamFusedRadius && !overlap(cube, out, need)) {
+    a.in = cube;
+    a.out = out;
+    return host::hip_status(launch_beam_fused<kBeamFusedRadius>(a, st), "beam kernel");
+  }
   const bool v4 = aligned4(cube, n_chan) && aligned4(out, n_chan) && aligned4(workspace, n_chan);
   const int V = v4 ? 4 : 1;
   // Work items of a pass: the other axis x runs of kBeamRun positions x columns.
@@ -212,16 +381,13 @@ iris_status iris_lv_mean(const float* cube, float* out, int32_t n1, int32_t n2, 
   iris_status s = check_cube(cube, out, n1, n2, n_chan);
   if (s != IRIS_OK) return s;
   if (axis != 0 && axis != 1) return host::fail(IRIS_E_INVALID_ARG, "axis must be 0 or 1");
-  const int64_t n_other = axis == 0 ? n2 : n1;
   const bool v4 = aligned4(cube, n_chan) && aligned4(out, n_chan);
+  const int64_t blocks = ((axis == 0 ? n2 : n1) * ((int64_t)n_chan / (v4 ? 4 : 1)) + 63) / 64;
+  if (blocks > 0x7FFFFFFF) return host::fail(IRIS_E_UNSUPPORTED, "cube too large for one launch");
   const hipStream_t st = (hipStream_t)stream;
-  if (v4)
-    hipLaunchKernelGGL(lv_mean_kernel<4>, dim3(grid_for(n_other * n_chan / 4)), dim3(256), 0, st,
-                       cube, out, (int64_t)n1, (int64_t)n2, (int64_t)n_chan, (int)axis);
-  else
-    hipLaunchKernelGGL(lv_mean_kernel<1>, dim3(grid_for(n_other * n_chan)), dim3(256), 0, st,
-                       cube, out, (int64_t)n1, (int64_t)n2, (int64_t)n_chan, (int)axis);
-  return host::hip_status((int)hipGetLastError(), "l,v mean kernel");
+  return host::hip_status(v4 ? launch_lv_mean<4>(cube, out, n1, n2, n_chan, axis, st)
+                             : launch_lv_mean<1>(cube, out, n1, n2, n_chan, axis, st),
+                          "l,v mean kernel");
 }
 
 }  // extern "C"

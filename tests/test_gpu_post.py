@@ -47,6 +47,24 @@ def test_beam_in_place_and_unaligned_match():
     assert torch.allclose(view, ref, rtol=1e-6, atol=1e-6)
 
 
+@pytest.mark.parametrize("shape,fwhm", [((7, 65, 33), 0.5), ((130, 64, 31), 7.06),
+                                        ((61, 129, 32), 7.2), ((3, 8, 70), 2.39),
+                                        ((200, 1, 5), 5.0)])
+def test_beam_tiles_and_radii(shape, fwhm):
+    # Tiles of 64 positions and 32 channels, segments shorter and longer than
+    # the halo, the widest fused radius (12) and the first beyond it. The in-place
+    # call takes the two passes, which sum the same taps in the same order.
+    say(f"[beam] shape={shape} fwhm={fwhm}")
+    a = _rand_cube(shape, 4)
+    t = torch.from_numpy(a).cuda()
+    out = rt.beam_convolve(t, fwhm)
+    two = rt.beam_convolve(t, fwhm, out=t)
+    torch.cuda.synchronize()
+    assert torch.equal(out, two)
+    assert M.err_inf(out.double().cpu().numpy(),
+                     post.beam_convolve(a.astype(np.float64), fwhm)) <= TOL_FWD
+
+
 @pytest.mark.parametrize("axis", [0, 1])
 @pytest.mark.parametrize("shape", [(33, 47, 64), (9, 128, 5)])
 def test_lv_mean_against_reference(shape, axis):
@@ -56,6 +74,16 @@ def test_lv_mean_against_reference(shape, axis):
     torch.cuda.synchronize()
     ref = post.lv_mean(a.astype(np.float64), axis)
     assert M.err_inf(out.double().cpu().numpy(), ref) <= TOL_FWD
+
+
+@pytest.mark.parametrize("axis", [0, 1])
+@pytest.mark.parametrize("shape", [(300, 4, 16), (4, 301, 3), (15, 16, 64)])
+def test_lv_mean_parts(shape, axis):
+    # The axis in 1, 2 and 16 parts, with remainders of the eight-load rounds.
+    a = _rand_cube(shape, 5)
+    out = rt.lv_mean(torch.from_numpy(a).cuda(), axis)
+    torch.cuda.synchronize()
+    assert M.err_inf(out.double().cpu().numpy(), post.lv_mean(a.astype(np.float64), axis)) <= TOL_FWD
 
 
 def test_beam_and_lv_of_a_synthesised_cube():
