@@ -319,6 +319,15 @@ iris_status iris_rt_adjoint(const iris_fields* fields, const iris_channels* chan
                             void* workspace, size_t workspace_bytes,
                             const iris_gradients* grads, void* stream);
 
+/* iris_rt_adjoint with the gradients stored as grad_dtype (iris_dtype): the
+ * arrays of `grads` hold that type's elements. Each gradient is computed as by
+ * iris_rt_adjoint and rounded once to FP32, then to the 16-bit types. For
+ * callers that hold their fields and gradients in the same narrower type. */
+iris_status iris_rt_adjoint_typed(const iris_fields* fields, const iris_channels* channels,
+                                  const iris_line* line, const iris_cotangents* cot,
+                                  int32_t ckpt_K, void* workspace, size_t workspace_bytes,
+                                  const iris_gradients* grads, int32_t grad_dtype, void* stream);
+
 /* ---- Autotuning -----------------------------------------------------------
  * The forward march packs G = 1, 2 or 4 sightlines into one wavefront (64/G
  * lanes each). iris_rt_autotune times the three on the given cube (writing

@@ -753,11 +753,8 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
         }
         const double gX = kLbar * cp.dkL_dX;
         const int64_t off = P.gat.base(pix) + (int64_t)s * P.gat.los;
-        gstore(P.grad[0] + off, glnn);
-        gstore(P.grad[1] + off, gT);
-        gstore(P.grad[2] + off, vbar);
-        gstore(P.grad[3] + off, gX);
-        if (GEN && has_td) gstore(P.grad[4] + off, gTd);
+        const double gr[5] = {glnn, gT, vbar, gX, gTd};
+        store_grads<GEN>(P, off, has_td, gr);
       }
       // Carry the composition of the whole round (the group's last lane).
       const int last = sub * W + W - 1;

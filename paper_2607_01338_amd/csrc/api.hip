@@ -17,7 +17,7 @@ static iris_status thin_adjoint_impl(const iris_fields* fields, const Geo& g,
                                      const iris_channels* channels, const iris_line* line,
                                      const iris_cotangents* cot, int32_t ckpt_K, void* workspace,
                                      size_t workspace_bytes, const iris_gradients* grads,
-                                     void* stream, int groups) {
+                                     void* stream, int groups, iris_dtype grad_dtype) {
   if (ckpt_K != 0)
     return fail(IRIS_E_INVALID_ARG, "optically thin transfer takes no checkpoints: ckpt_K must be 0");
   if (line->units == IRIS_UNITS_TB)
@@ -54,6 +54,7 @@ static iris_status thin_adjoint_impl(const iris_fields* fields, const Geo& g,
   p.grad[2] = grads->g_v_los;
   p.grad[3] = grads->g_x_tracer;
   p.grad[4] = fields->t_dust ? grads->g_t_dust : nullptr;
+  p.grad_dtype = (int32_t)grad_dtype;
   p.dtype = (int32_t)fields->dtype;
   p.groups = groups;
   return hip_status(launch_thin_adjoint(p, line->integrator == IRIS_INTEGRATOR_SMOOTH, groups,
@@ -64,7 +65,7 @@ static iris_status thin_adjoint_impl(const iris_fields* fields, const Geo& g,
 iris_status adjoint_impl(const iris_fields* fields, const iris_channels* channels,
                          const iris_line* line, const iris_cotangents* cot, int32_t ckpt_K,
                          void* workspace, size_t workspace_bytes, const iris_gradients* grads,
-                         void* stream, int groups) {
+                         void* stream, int groups, iris_dtype grad_dtype) {
   Geo g;
   iris_status s;
   if ((s = check_fields(fields, &g)) != IRIS_OK) return s;
@@ -79,7 +80,7 @@ iris_status adjoint_impl(const iris_fields* fields, const iris_channels* channel
     return fail(IRIS_E_INVALID_ARG, "g_t_dust is NULL while t_dust is given");
   if (line->transfer == IRIS_TRANSFER_THIN)
     return thin_adjoint_impl(fields, g, channels, line, cot, ckpt_K, workspace, workspace_bytes,
-                             grads, stream, groups);
+                             grads, stream, groups, grad_dtype);
   if (!valid_K(ckpt_K) || ckpt_K == 0)
     return fail(IRIS_E_INVALID_ARG, "adjoint needs ckpt_K in {8,16,32,64}");
   const WsLayout w = ws_layout(fields, g, channels->n_chan, ckpt_K);
@@ -108,22 +109,22 @@ iris_status adjoint_impl(const iris_fields* fields, const iris_channels* channel
              : adjoint_groups(fields, channels, line, fc, ckpt_K) == 0)
     return fail(IRIS_E_UNSUPPORTED, "adjoint needs %zu bytes of LDS per workgroup (n_chan %d, K %d)",
                 (size_t)adj_lds_floats(C, ckpt_K, groups ? groups : 1, gen) * 4, C, ckpt_K);
-  double* gsoa[5] = {grads->g_ln_nh2, grads->g_t_kin, grads->g_v_los, grads->g_x_tracer,
+  void* gsoa[5] = {grads->g_ln_nh2, grads->g_t_kin, grads->g_v_los, grads->g_x_tracer,
                      fields->t_dust ? grads->g_t_dust : nullptr};
   if (!in_place)
     for (int i = 0; i < g.n_fields; ++i)
-      gsoa[i] = (double*)((char*)workspace + w.grad) + i * g.n_cells;
+      gsoa[i] = (char*)workspace + w.grad + i * g.n_cells * elem_size(grad_dtype);
   const iris::AdjParams p =
       adj_params(fields, g, channels, line, cot, ckpt_K, fsl, at, (char*)workspace + w.tab,
                  (const float*)((char*)workspace + w.ck_state),
-                 (const double*)((char*)workspace + w.ck_scal), gsoa, at, groups);
+                 (const double*)((char*)workspace + w.ck_scal), gsoa, at, groups, grad_dtype);
   if ((s = hip_status(iris::launch_adjoint(fields->dtype, p, stream), "adjoint kernel")) != IRIS_OK)
     return s;
   if (in_place) return IRIS_OK;
   // Sightline-major -> native layout: the inverse of the ingest transpose.
-  double* dst[5] = {grads->g_ln_nh2, grads->g_t_kin, grads->g_v_los, grads->g_x_tracer,
+  void* dst[5] = {grads->g_ln_nh2, grads->g_t_kin, grads->g_v_los, grads->g_x_tracer,
                     fields->t_dust ? grads->g_t_dust : nullptr};
-  return hip_status(iris::launch_layout(gradient_layout(fields, g, gsoa, dst), stream),
+  return hip_status(iris::launch_layout(gradient_layout(fields, g, gsoa, dst, grad_dtype), stream),
                     "gradient layout kernel");
 }
 
@@ -200,6 +201,17 @@ iris_status iris_rt_adjoint(const iris_fields* fields, const iris_channels* chan
   clear_error();
   return adjoint_impl(fields, channels, line, cot, ckpt_K, workspace, workspace_bytes, grads,
                       stream, 0);
+}
+
+iris_status iris_rt_adjoint_typed(const iris_fields* fields, const iris_channels* channels,
+                                  const iris_line* line, const iris_cotangents* cot,
+                                  int32_t ckpt_K, void* workspace, size_t workspace_bytes,
+                                  const iris_gradients* grads, int32_t grad_dtype, void* stream) {
+  clear_error();
+  if (grad_dtype < IRIS_F64 || grad_dtype > IRIS_F16)
+    return fail(IRIS_E_INVALID_ARG, "unknown gradient dtype %d", grad_dtype);
+  return adjoint_impl(fields, channels, line, cot, ckpt_K, workspace, workspace_bytes, grads,
+                      stream, 0, (iris_dtype)grad_dtype);
 }
 
 iris_status iris_rt_autotune_adjoint(const iris_fields* fields, const iris_channels* channels,

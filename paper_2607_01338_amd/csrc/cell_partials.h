@@ -9,6 +9,39 @@
 
 namespace iris {
 
+// Stores a cell's gradients (the fifth where the launch has one) in the
+// launch's gradient type, through FP32 for the 16-bit ones. Storing FP64 for a
+// caller that wants FP32 costs its conversion pass: on a 256^3 cube 4 x 47 us
+// after an adjoint of 1.8 ms.
+template <bool FIFTH>
+__device__ __forceinline__ void store_grads(const AdjParams& P, int64_t off, bool fifth,
+                                            const double (&g)[5]) {
+  const int n = FIFTH && fifth ? 5 : 4;
+  if (P.grad_dtype == IRIS_F64) {
+#pragma unroll
+    for (int i = 0; i < (FIFTH ? 5 : 4); ++i)
+      if (i < n) gstore((double*)P.grad[i] + off, g[i]);
+    return;
+  }
+  float f[5];
+#pragma unroll
+  for (int i = 0; i < 5; ++i) f[i] = (float)g[i];
+  if (P.grad_dtype == IRIS_F32) {
+#pragma unroll
+    for (int i = 0; i < (FIFTH ? 5 : 4); ++i)
+      if (i < n) gstore((float*)P.grad[i] + off, f[i]);
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < (FIFTH ? 5 : 4); ++i) {
+    const uint32_t u = __float_as_uint(f[i]);
+    const uint32_t bf = f[i] == f[i] ? (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16 : 0x7FC0u;
+    const uint16_t h = __builtin_bit_cast(uint16_t, (_Float16)f[i]);
+    if (i < n)
+      gstore((uint16_t*)P.grad[i] + off, P.grad_dtype == IRIS_F16 ? h : (uint16_t)bf);
+  }
+}
+
 struct CellPartials {
   double kL;       // line-centre optical depth
   double dkL_dT;   // total d kappa_L / d T (populations, stimulated emission, 1/b)

@@ -78,10 +78,10 @@ struct WsLayout {
 WsLayout ws_layout(const iris_fields* f, const Geo& g, int n_chan, int K);
 
 // Transpose descriptor that lays the fields of `f` out sightline-major at dst
-// (n_fields arrays of n_cells elements), and its inverse for FP64 gradients.
+// (n_fields arrays of n_cells elements), and its inverse for gradients.
 LayoutParams field_layout(const iris_fields* f, const Geo& g, void* dst);
-LayoutParams gradient_layout(const iris_fields* f, const Geo& g, double* const src[5],
-                             double* const dst[5]);
+LayoutParams gradient_layout(const iris_fields* f, const Geo& g, void* const src[5],
+                             void* const dst[5], iris_dtype dt = IRIS_F64);
 
 // Sightlines per wavefront of the forward march for this cube: the override
 // IRIS_RT_SIGHTLINES_PER_WAVE, else an autotuned choice recorded for the
@@ -110,11 +110,12 @@ inline int adj_lds_floats(int n_chan, int K, int groups, bool general) {
 }
 bool adjoint_fits(int n_chan, int K, int groups, bool general);
 // The adjoint of one cube after the forward that wrote its checkpoints into
-// `workspace`, with a fixed packing (0: adjoint_groups).
+// `workspace`, with a fixed packing (0: adjoint_groups); the gradient arrays
+// hold elements of grad_dtype.
 iris_status adjoint_impl(const iris_fields* fields, const iris_channels* channels,
                          const iris_line* line, const iris_cotangents* cot, int32_t ckpt_K,
                          void* workspace, size_t workspace_bytes, const iris_gradients* grads,
-                         void* stream, int groups);
+                         void* stream, int groups, iris_dtype grad_dtype = IRIS_F64);
 
 // Kernel parameters of one cube. `fsl` are the field arrays addressed by
 // `at`, `tab` the temperature tables; the checkpoint pointers may be NULL
@@ -126,8 +127,8 @@ FwdParams fwd_params(const iris_fields* f, const Geo& g, const iris_channels* ch
 AdjParams adj_params(const iris_fields* f, const Geo& g, const iris_channels* ch,
                      const iris_line* L, const iris_cotangents* cot, int K,
                      const void* const fsl[5], const SightAddr& at, const void* tab,
-                     const float* ck_state, const double* ck_scal, double* const grad[5],
-                     const SightAddr& gat, int groups = 0);
+                     const float* ck_state, const double* ck_scal, void* const grad[5],
+                     const SightAddr& gat, int groups = 0, iris_dtype grad_dtype = IRIS_F64);
 
 // Forward of one cube into a caller workspace with a fixed number of
 // sightlines per wavefront (0: choose_groups).

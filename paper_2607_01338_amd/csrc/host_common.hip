@@ -302,15 +302,15 @@ LayoutParams field_layout(const iris_fields* f, const Geo& g, void* dst) {
   return lp;
 }
 
-LayoutParams gradient_layout(const iris_fields* f, const Geo& g, double* const src[5],
-                             double* const dst[5]) {
+LayoutParams gradient_layout(const iris_fields* f, const Geo& g, void* const src[5],
+                             void* const dst[5], iris_dtype dt) {
   LayoutParams lp{};
   for (int i = 0; i < g.n_fields; ++i) {
     lp.src[i] = src[i];
     lp.dst[i] = dst[i];
   }
   lp.n_fields = g.n_fields;
-  lp.elem = 8;
+  lp.elem = (int)elem_size(dt);
   if (f->axis == 1) {
     lp.batch = f->nx;
     lp.rows = f->nz;
@@ -530,8 +530,8 @@ FwdParams fwd_params(const iris_fields* f, const Geo& g, const iris_channels* ch
 AdjParams adj_params(const iris_fields* f, const Geo& g, const iris_channels* ch,
                      const iris_line* L, const iris_cotangents* cot, int K,
                      const void* const fsl[5], const SightAddr& at, const void* tab,
-                     const float* ck_state, const double* ck_scal, double* const grad[5],
-                     const SightAddr& gat, int groups) {
+                     const float* ck_state, const double* ck_scal, void* const grad[5],
+                     const SightAddr& gat, int groups, iris_dtype grad_dtype) {
   AdjParams p{};
   for (int i = 0; i < 5; ++i) p.f[i] = fsl[i];
   p.at = at;
@@ -555,6 +555,7 @@ AdjParams adj_params(const iris_fields* f, const Geo& g, const iris_channels* ch
   p.ck_scal = ck_scal;
   for (int i = 0; i < 5; ++i) p.grad[i] = grad[i];
   p.gat = gat;
+  p.grad_dtype = (int32_t)grad_dtype;
   return p;
 }
 

@@ -149,8 +149,9 @@ struct AdjParams {
   int32_t tape_passes;    // W-lane passes the LDS tape holds per sightline
   const float* ck_state;
   const double* ck_scal;
-  double* grad[5];        // per stored field, addressed by `gat`
+  void* grad[5];          // per stored field, elements of grad_dtype addressed by `gat`
   SightAddr gat;
+  int32_t grad_dtype;     // iris_dtype of the gradients
   int32_t dtype;          // iris_dtype of the fields (used by batched launches)
   int32_t groups;         // sightlines per wavefront: 1, 2 or 4
 };

@@ -453,13 +453,13 @@ iris_status build_plan(const iris_cube* cubes, int n, const iris_line* L, int fl
               (sizeof(float) * kWavesPerBlock)));
     samples += g.n_cells * cb.channels.n_chan;
     if (adj) {
-      double* const gtd = cb.fields.t_dust ? cb.grads.g_t_dust : nullptr;
-      double* gsoa[5] = {cb.grads.g_ln_nh2, cb.grads.g_t_kin, cb.grads.g_v_los,
+      void* const gtd = cb.fields.t_dust ? cb.grads.g_t_dust : nullptr;
+      void* gsoa[5] = {cb.grads.g_ln_nh2, cb.grads.g_t_kin, cb.grads.g_v_los,
                          cb.grads.g_x_tracer, gtd};
       if (!in_place) {
         for (int k = 0; k < g.n_fields; ++k)
           gsoa[k] = (double*)(ws + wl[i].grad) + k * g.n_cells;
-        double* dst[5] = {cb.grads.g_ln_nh2, cb.grads.g_t_kin, cb.grads.g_v_los,
+        void* dst[5] = {cb.grads.g_ln_nh2, cb.grads.g_t_kin, cb.grads.g_v_los,
                           cb.grads.g_x_tracer, gtd};
         const LayoutParams lp = gradient_layout(&cb.fields, g, gsoa, dst);
         TransposeJob j{};

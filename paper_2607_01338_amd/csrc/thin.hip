@@ -436,11 +436,8 @@ __global__ __launch_bounds__(256) void thin_adj_kernel(const AdjParams P, int sm
       if (has_td) gTd = bDe * kDn * planck_rj_dT(c, (double)in.Td);
       else gT += bDe * kDn * cp.dJ_dT;
       const int64_t off = P.gat.base(pix) + (int64_t)s * P.gat.los;
-      gstore(P.grad[0] + off, glnn);
-      gstore(P.grad[1] + off, gT);
-      gstore(P.grad[2] + off, gv);
-      gstore(P.grad[3] + off, gX);
-      if (has_td) gstore(P.grad[4] + off, gTd);
+      const double gr[5] = {glnn, gT, gv, gX, gTd};
+      store_grads<GEN>(P, off, has_td, gr);
     }
     wave_order();
   }

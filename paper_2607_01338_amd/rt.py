@@ -158,6 +158,10 @@ _SIGNATURES = {
                          ctypes.POINTER(Cotangents), ctypes.c_int32, ctypes.c_void_p,
                          ctypes.c_size_t, ctypes.POINTER(Gradients), ctypes.c_void_p],
                         ctypes.c_int),
+    "iris_rt_adjoint_typed": ([ctypes.POINTER(Fields), ctypes.POINTER(ChannelsC),
+                               ctypes.POINTER(LineC), ctypes.POINTER(Cotangents), ctypes.c_int32,
+                               ctypes.c_void_p, ctypes.c_size_t, ctypes.POINTER(Gradients),
+                               ctypes.c_int32, ctypes.c_void_p], ctypes.c_int),
     "iris_rt_autotune": ([ctypes.POINTER(Fields), ctypes.POINTER(ChannelsC), ctypes.POINTER(LineC),
                           ctypes.POINTER(Outputs), ctypes.c_void_p, ctypes.c_size_t,
                           ctypes.c_void_p, ctypes.POINTER(ctypes.c_int32)], ctypes.c_int),
@@ -390,7 +394,7 @@ def iris_rt_autotune_adjoint(ln_nh2, t_kin, v_los, x_tracer, t_dust=None, *, axi
 
 
 def _adjoint_call(ln_nh2, t_kin, v_los, x_tracer, t_dust, axis, cell_cm, channels, line, cot,
-                  ckpt_K, workspace, tune):
+                  ckpt_K, workspace, tune, grad_dtype=torch.float64):
     lib = load_library()
     f = _fields_struct(ln_nh2, t_kin, v_los, x_tracer, t_dust, axis, cell_cm)
     ch = channels.c() if isinstance(channels, Channels) else Channels(*channels).c()
@@ -406,19 +410,19 @@ def _adjoint_call(ln_nh2, t_kin, v_los, x_tracer, t_dust, axis, cell_cm, channel
             cots[k] = t.contiguous()
     cs = Cotangents(*(_ptr(cots.get(k)) for k in "TCDLB"))
     names = ["ln_nh2", "t_kin", "v_los", "x_tracer"] + (["t_dust"] if t_dust is not None else [])
-    grads = {n: torch.empty(ln_nh2.shape, dtype=torch.float64, device=dev) for n in names}
+    grads = {n: torch.empty(ln_nh2.shape, dtype=grad_dtype, device=dev) for n in names}
     gs = Gradients(*(_ptr(grads.get(n)) for n in ("ln_nh2", "t_kin", "v_los", "x_tracer",
                                                    "t_dust")))
     if workspace is None:
         workspace = torch.empty(max(workspace_bytes(f, ch, ckpt_K), 1), dtype=torch.uint8,
                                 device=dev)
     args = (ctypes.byref(f), ctypes.byref(ch), ctypes.byref(ln), ctypes.byref(cs), int(ckpt_K),
-            _ptr(workspace), workspace.numel(), ctypes.byref(gs), _stream(dev))
+            _ptr(workspace), workspace.numel(), ctypes.byref(gs))
     if not tune:
-        _check(lib.iris_rt_adjoint(*args))
+        _check(lib.iris_rt_adjoint_typed(*args, _DTYPES[grad_dtype], _stream(dev)))
         return grads
     g = ctypes.c_int32(0)
-    _check(lib.iris_rt_autotune_adjoint(*args, ctypes.byref(g)))
+    _check(lib.iris_rt_autotune_adjoint(*args, _stream(dev), ctypes.byref(g)))
     return g.value, grads
 
 
@@ -685,6 +689,9 @@ class IrisRT(torch.autograd.Function):
     @staticmethod
     def forward(ctx, ln_nh2, t_kin, v_los, x_tracer, t_dust, axis, cell_cm, channels, line,
                 ckpt_K):
+        # Outputs the loss does not use stay None in the backward: no zero cubes
+        # are made, written and read for them.
+        ctx.set_materialize_grads(False)
         need_grad = any(ctx.needs_input_grad[:5])
         # Optically thin transfer marches nothing and takes no checkpoints.
         thin = transfer_code((line or {}).get("transfer", TRANSFER_THICK)) == TRANSFER_THIN
@@ -701,12 +708,10 @@ class IrisRT(torch.autograd.Function):
         axis, cell_cm, channels, line, K, ws = ctx.meta
         cot = {k: (g.float().contiguous() if g is not None else None)
                for k, g in zip("TCDLB", (gT, gC, gD, gL, gB))}
-        g = iris_rt_adjoint(ln_nh2, t_kin, v_los, x_tracer, t_dust, axis=axis, cell_cm=cell_cm,
-                            channels=channels, line=line, cot=cot, ckpt_K=K, workspace=ws)
-        dt = ln_nh2.dtype
-        gtd = g["t_dust"].to(dt) if t_dust is not None else None
-        return (g["ln_nh2"].to(dt), g["t_kin"].to(dt), g["v_los"].to(dt), g["x_tracer"].to(dt),
-                gtd, None, None, None, None, None)
+        g = _adjoint_call(ln_nh2, t_kin, v_los, x_tracer, t_dust, axis, cell_cm, channels, line,
+                          cot, K, ws, tune=False, grad_dtype=ln_nh2.dtype)
+        return (g["ln_nh2"], g["t_kin"], g["v_los"], g["x_tracer"], g.get("t_dust"), None, None,
+                None, None, None)
 
 
 def synthesize(ln_nh2, t_kin, v_los, x_tracer, t_dust=None, *, axis, cell_cm, channels, line=None,

@@ -422,3 +422,32 @@ def test_adjoint_through_dust_opaque_sightlines():
         say(f"      {f}: max |gpu| {np.max(np.abs(g[f])):.2e}, max |oracle| "
             f"{np.max(np.abs(ref[f])):.2e}")
         assert np.max(np.abs(g[f])) < 1e-6 and np.max(np.abs(ref[f])) < 1e-6, f
+
+
+@pytest.mark.parametrize("layout", ["", "transpose"])
+@pytest.mark.parametrize("transfer", ["thick", "thin"])
+@pytest.mark.parametrize("dt", ["f64", "f32", "bf16", "f16"])
+def test_gradients_in_the_type_of_the_fields(dt, transfer, layout, monkeypatch):
+    # Stored in the fields' type, the gradients are the FP64 ones rounded; a
+    # loss of [L] alone leaves the other cotangents out.
+    cube = W.make_cube((5, 9, 19), 1, W.Channels(48, -24.0, 1.0), seed=71, v_rms_kms=6.0,
+                       t_dust=True)
+    say(f"[adj] gradients stored as {dt}, {transfer} {layout}")
+    if layout:
+        monkeypatch.setenv("IRIS_RT_FIELD_LAYOUT", layout)
+    dev = to_device(cube, dt)
+    names = FIELDS + ("t_dust",)
+    leaves = [dev[k].clone().requires_grad_(True) for k in names]
+    line = line_dict(transfer=transfer)
+    args = dict(axis=1, cell_cm=cube.cell_cm, channels=channels_of(cube), line=line)
+    out = rt.synthesize(*leaves, ckpt_K=8, **args)
+    g = torch.randn(out["L"].shape, generator=torch.Generator().manual_seed(3)).cuda()
+    got = torch.autograd.grad((out["L"] * g).sum(), leaves)
+    K = 0 if transfer == "thin" else 8
+    ws = rt.iris_rt_forward(*(dev[k] for k in names), ckpt_K=K, **args).get("_workspace")
+    ref = rt.iris_rt_adjoint(*(dev[k] for k in names), cot={"L": g}, ckpt_K=K, workspace=ws,
+                             **args)
+    torch.cuda.synchronize()
+    for k, a in zip(names, got):
+        assert a.dtype == dev[k].dtype
+        assert torch.equal(a, ref[k].to(a.dtype)), k
