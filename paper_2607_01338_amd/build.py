@@ -35,6 +35,12 @@ CFLAGS = [
 ]
 
 
+# Per source: the march keeps more wavefronts resident without loop-invariant
+# code motion on machine code, which holds the constants of its rarely taken
+# branches in vector registers across the whole march (107 -> 76 registers).
+SOURCE_FLAGS = {"forward.hip": ["-mllvm", "-disable-machine-licm"]}
+
+
 # Sources whose host code validates arguments, folds constants, carves
 # workspaces, reads molecular data and sets up plans: the checking build
 # compiles their host side with AddressSanitizer and UBSan.
@@ -46,7 +52,8 @@ SANITIZE_HOST = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize
 
 def _compile(src: str, extra=(), obj_dir: str = OBJ) -> str:
     obj = os.path.join(obj_dir, os.path.basename(src) + ".o")
-    cmd = [HIPCC, *CFLAGS, *extra, "-c", src, "-o", obj]
+    cmd = [HIPCC, *CFLAGS, *SOURCE_FLAGS.get(os.path.basename(src), ()), *extra, "-c", src, "-o",
+           obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed on {src}:\n{r.stdout}\n{r.stderr}")

@@ -113,10 +113,10 @@ __device__ __forceinline__ CellPartials cell_partials(const Folded& c, double ln
                                                       double X) {
   CellPartials p;
   if (cell_partials_tab<GEN>(c, lnn, T, X, p)) return p;
-  const double n = exp(lnn);
+  const double n = exp_rare(lnn);
   // Z = sum (2J+1) q^{J(J+1)} and E-weighted sum for dZ/dT, with
   // q^{J(J+1)} = e^{-E_J/T}, E_J = theta J(J+1), theta = th2 / log2(e).
-  const double q = exp2(-c.th2 / T);
+  const double q = exp_rare(-c.th2 * 0.69314718055994530942 / T);
   const double q2 = q * q;
   const double theta = c.th2 * 0.69314718055994530942;
   double Z = 0.0, ZE = 0.0, r = 1.0, m = q2, rl = 0.0;
@@ -133,8 +133,8 @@ __device__ __forceinline__ CellPartials cell_partials(const Folded& c, double ln
   // d ln f_l / dT = E_l/T^2 - <E>/T^2, <E> = theta ZE / Z.
   const double dlnfl = (El - theta * ZE / Z) / (T * T);
   const double dE = (double)c.dE;
-  const double em = exp(-dE / T);
-  const double stim = -expm1(-dE / T);
+  const double em = exp_rare(-dE / T);
+  const double stim = -expm1_rare(-dE / T);
   const double dlnstim = -em * dE / (T * T) / stim;
   const double b2 = (double)c.bT * T + (double)c.bt2;
   p.b = sqrt(b2);
@@ -150,12 +150,12 @@ __device__ __forceinline__ CellPartials cell_partials(const Folded& c, double ln
   }
   const double T0 = (double)c.T0;
   const double x = T0 / T;
-  const double J = T0 / expm1(x);
-  p.dJ_dT = J * J * exp(x) / (T * T);
+  const double J = T0 / expm1_rare(x);
+  p.dJ_dT = J * J * exp_rare(x) / (T * T);
   // JL = T0 / (e^y - 1), y = dE/T: dJL/dT = JL^2 e^y dE / (T0 T^2).
   const double y = dE / T;
-  const double JL = T0 / expm1(y);
-  p.dJL_dT = JL * JL * exp(y) * dE / (T0 * T * T);
+  const double JL = T0 / expm1_rare(y);
+  p.dJL_dT = JL * JL * exp_rare(y) * dE / (T0 * T * T);
   p.dkL_dlnn = p.dJL_dlnn = 0.0;
   p.line_src = true;
   p.kD_free = (double)c.kD * n;
@@ -178,8 +178,8 @@ __device__ __forceinline__ double planck_rj_dT(const Folded& c, double T) {
   }
   if (!(T > 0.0)) return 0.0;
   const double x = (double)c.T0 / T;
-  const double J = (double)c.T0 / expm1(x);
-  return J * J * exp(x) / (T * T);
+  const double J = (double)c.T0 / expm1_rare(x);
+  return J * J * exp_rare(x) / (T * T);
 }
 
 

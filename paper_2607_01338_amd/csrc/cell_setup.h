@@ -25,6 +25,7 @@ struct CellOut {
   float A, R, lk;
   float df;      // (float)(kstart - kc)
   float c0;
+  float m;       // c0 / A: t of the window's channel j is (j + m) A
   int kstart;    // first channel of the line window
   int nwin;      // channels in the window; 0 = the cell carries no line
 };
@@ -55,6 +56,24 @@ __device__ __forceinline__ RawCell<FT> fetch_cell(const FT* const* f, int64_t of
   return r;
 }
 
+// The same at a byte offset from the (uniform) field bases, of 32 bits where
+// every offset of the launch fits.
+template <typename FT, typename Off>
+__device__ __forceinline__ RawCell<FT> fetch_cell_at(const void* const* base, Off bytes,
+                                                     bool valid, bool has_td) {
+  using S = typename std::conditional<std::is_same<FT, bf16_t>::value, uint16_t, FT>::type;
+  auto get = [&](int i) { return __builtin_bit_cast(FT, gload_at<S>(base[i], bytes)); };
+  RawCell<FT> r{};
+  if (valid) {
+    r.lnn = get(0);
+    r.T = get(1);
+    r.v = get(2);
+    r.X = get(3);
+    r.Td = has_td ? get(4) : r.T;
+  }
+  return r;
+}
+
 // Invalid cells (beyond the sightline or of a dead group) get harmless values.
 template <typename FT>
 __device__ __forceinline__ CellIn decode_cell(const RawCell<FT>& r, bool valid) {
@@ -80,12 +99,18 @@ __device__ __forceinline__ CellIn decode_cell(const RawCell<FT>& r, bool valid) 
 template <typename FT>
 struct Loader {
   using Raw = RawCell<FT>;
+  const void* const* b;
   const FT* f[5];
   bool has_td;
-  __device__ __forceinline__ Loader(const void* const* base, int64_t first) {
+  __device__ __forceinline__ Loader(const void* const* base, int64_t first) : b(base) {
 #pragma unroll
     for (int i = 0; i < 5; ++i) f[i] = base[i] ? (const FT*)base[i] + first : nullptr;
     has_td = base[4] != nullptr;
+  }
+  __device__ __forceinline__ uint32_t elem_bytes() const { return sizeof(FT); }
+  template <typename Off>
+  __device__ __forceinline__ Raw fetch_at(Off bytes, bool valid) const {
+    return fetch_cell_at<FT>(b, bytes, valid, has_td);
   }
   __device__ __forceinline__ Raw fetch(int64_t off, bool valid) const {
     return fetch_cell<FT>(f, off, valid, has_td);
@@ -117,8 +142,7 @@ struct DynLoader {
       : base(b), first(fst), dt(dtype) {}
 
   template <typename FT>
-  __device__ __forceinline__ Raw fetch_bits(int64_t off, bool valid) const {
-    const RawCell<FT> r = Loader<FT>(base, first).fetch(off, valid);
+  static __device__ __forceinline__ Raw pack(const RawCell<FT>& r) {
     Raw w;
     if constexpr (sizeof(FT) == 8) {
       w.lnn = __float_as_uint((float)r.lnn);
@@ -140,6 +164,23 @@ struct DynLoader {
       w.v = bits16(r.v);
     }
     return w;
+  }
+  template <typename FT>
+  __device__ __forceinline__ Raw fetch_bits(int64_t off, bool valid) const {
+    return pack<FT>(Loader<FT>(base, first).fetch(off, valid));
+  }
+  __device__ __forceinline__ uint32_t elem_bytes() const {
+    return dt == IRIS_F64 ? 8u : dt == IRIS_F32 ? 4u : 2u;
+  }
+  template <typename Off>
+  __device__ __forceinline__ Raw fetch_at(Off bytes, bool valid) const {
+    const bool td = base[4] != nullptr;
+    switch (dt) {
+      case IRIS_F64: return pack<double>(fetch_cell_at<double>(base, bytes, valid, td));
+      case IRIS_BF16: return pack<bf16_t>(fetch_cell_at<bf16_t>(base, bytes, valid, td));
+      case IRIS_F16: return pack<_Float16>(fetch_cell_at<_Float16>(base, bytes, valid, td));
+      default: return pack<float>(fetch_cell_at<float>(base, bytes, valid, td));
+    }
   }
   static __device__ __forceinline__ uint32_t bits16(bf16_t x) { return x.bits; }
   static __device__ __forceinline__ uint32_t bits16(_Float16 x) {
@@ -201,21 +242,55 @@ __device__ __forceinline__ bool tab_coord(float T, int& idx, float& t) {
 }
 
 __device__ __forceinline__ float tab_eval(const Folded& c, int which, int idx, float t) {
-  const float4 q = gload((const float4*)c.tab + which * kTabN + idx);
+  const gv4f q = gload_at<gv4f>(c.tab, (uint32_t)((which * kTabN + idx) * 16));
   return fmaf(t, fmaf(t, fmaf(t, q.w, q.z), q.y), q.x);
+}
+
+// Exponentials of the rare cells outside the tables, FP64 to a few ulp:
+// e^x = (1 + p) 2^n, |x - n ln 2| <= ln 2 / 2, p from the exponential series.
+// A loop on purpose: the polynomial constants of an unrolled exponential would
+// be kept in registers throughout the march (about 20 of them, a wavefront per
+// SIMD less).
+struct ExpParts {
+  double p;
+  int n;
+};
+__device__ __forceinline__ ExpParts exp_parts(double x) {
+  const double xc = fmin(fmax(x, -2000.0), 2000.0);
+  const double n = rint(xc * 1.44269504088896340736);
+  double r = fma(n, -0x1.62e42fep-1, xc);  // ln 2: 28 bits, then the rest
+  r = fma(n, -0x1.f473de6af278fp-30, r);
+  double s = 1.0;
+#pragma unroll 1
+  for (int k = 16; k >= 2; --k) s = fma(r / (double)k, s, 1.0);
+  return {r * s, (int)n};
+}
+__device__ __forceinline__ double exp_rare(double x) {
+  const ExpParts e = exp_parts(x);
+  return ldexp(1.0 + e.p, e.n);
+}
+__device__ __forceinline__ double expm1_rare(double x) {
+  const ExpParts e = exp_parts(x);
+  return ldexp(e.p, e.n) + (ldexp(1.0, e.n) - 1.0);
 }
 
 // Direct evaluation (FP64) for temperatures outside the tables.
 __device__ __forceinline__ void temp_direct(const Folded& c, float Tf, float& FL, float& J,
                                          float& JL) {
   const double T = (double)Tf;
-  const double theta = c.th2 * 0.69314718055994530942;
-  double Z = 0.0;
-  for (int j = 0; j <= c.j_max; ++j) Z += (2.0 * j + 1.0) * exp(-theta * j * (j + 1.0) / T);
-  const double El = theta * c.j_l * (c.j_l + 1.0);
-  FL = (float)(c.g_l * exp(-El / T) * -expm1(-(double)c.dE / T) / Z);
-  J = (float)((double)c.T0 / expm1((double)c.T0 / T));
-  JL = (float)((double)c.T0 / expm1((double)c.dE / T));
+  // Z = sum (2J+1) q^{J(J+1)}, q = e^{-theta/T}, by the powers of q^2.
+  const double q = exp_rare(-c.th2 * 0.69314718055994530942 / T);
+  const double q2 = q * q;
+  double Z = 0.0, r = 1.0, m = q2, rl = 0.0;
+  for (int j = 0; j <= c.j_max; ++j) {
+    if (j == c.j_l) rl = r;
+    Z = fma(2.0 * j + 1.0, r, Z);
+    r *= m;
+    m *= q2;
+  }
+  FL = (float)(c.g_l * rl * -expm1_rare(-(double)c.dE / T) / Z);
+  J = (float)((double)c.T0 / expm1_rare((double)c.T0 / T));
+  JL = (float)((double)c.T0 / expm1_rare((double)c.dE / T));
   if (!(Tf > 0.f)) FL = J = JL = 0.f;
 }
 
@@ -348,6 +423,8 @@ __device__ __forceinline__ CellOut cell_setup(const Folded& c, const CellIn& in,
     o.df = 0.f;
   }
   o.c0 = fmaf(o.df, o.A, -o.R);
+  // From the line centre in FP64, rounded once.
+  o.m = (float)((double)klo - fma(in.v - c.v_lo, c.inv_dv, -0.5));
   return o;
 }
 
@@ -364,11 +441,26 @@ __device__ __forceinline__ CellOut cell_setup(const Folded& c, const CellIn& in,
 // exponential is under 2e-6 of the step; the subtraction is exact while
 // 2^{-x} >= 1/2).
 constexpr float kSeriesX = 0.044f;
-__device__ __forceinline__ float formal_line_step(float ps, float g, float x) {
+__device__ __forceinline__ float line_absorbed(float x) {  // 1 - e^{-tau}
   float q = fmaf(x, 0.0555041087f, -0.2402265070f);  // (ln 2)^3/6, -(ln 2)^2/2
   q = fmaf(x, q, 0.6931471806f);                      // ln 2
-  const float om = x < kSeriesX ? x * q : 1.f - ex2(-x);  // 1 - e^{-tau}
-  return fmaf(-(ps + g), om, ps);
+  return x < kSeriesX ? x * q : 1.f - ex2(-x);
+}
+__device__ __forceinline__ float formal_line_step(float ps, float g, float x) {
+  return fmaf(-(ps + g), line_absorbed(x), ps);
+}
+
+// A step whose depth is at most kFaintTau everywhere in the window needs no
+// exponential and no choice: 1 - e^{-tau} = x q(x), q the cubic of least
+// relative error on [0, kFaintTau log2 e] (9.2e-7 at most, without bias,
+// against the 1.2e-6 that the series above reaches at its end). Three
+// multiply-adds in place of two, an exponential, a subtraction, a compare and a
+// select. The next degree reaches 0.5 for one more multiply-add per sample.
+constexpr float kFaintTau = 0.35f;
+__device__ __forceinline__ float faint_absorbed_over_x(float x) {
+  float q = fmaf(x, -0.00836536567658186f, 0.05511477589607239f);
+  q = fmaf(x, q, -0.24018700420856476f);
+  return fmaf(x, q, 0.6931465268135071f);
 }
 
 }  // namespace iris

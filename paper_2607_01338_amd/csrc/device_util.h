@@ -30,6 +30,14 @@ template <typename T>
 __device__ __forceinline__ void gstore(T* p, T v) {
   *(__attribute__((address_space(1))) T*)p = v;
 }
+// At a byte offset from a wave-uniform base: the base stays in scalar
+// registers, and a 32-bit offset needs no 64-bit address arithmetic per lane.
+template <typename T, typename Off>
+__device__ __forceinline__ T gload_at(const void* base, Off bytes) {
+  return *(const __attribute__((address_space(1))) T*)((const __attribute__((
+                                                           address_space(1))) char*)base +
+                                                       bytes);
+}
 typedef float gv4f __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float4 gload(const float4* p) {
   const gv4f v = *(const __attribute__((address_space(1))) gv4f*)p;
@@ -149,11 +157,24 @@ constexpr int kDppRowShr = 0x110;
 constexpr int kDppRowBcast15 = 0x142;
 constexpr int kDppRowBcast31 = 0x143;
 constexpr int kDppWaveShr1 = 0x138;
+constexpr int kDppRowNewBcast = 0x150;  // + n: lane n of each row of 16 to the whole row
 
 template <int Ctrl, int RowMask>
 __device__ __forceinline__ float dpp_f32(float x) {
   return __int_as_float(
       __builtin_amdgcn_update_dpp(0, __float_as_int(x), Ctrl, RowMask, 0xF, false));
+}
+
+// Lane N of each row of 16 lanes, in the whole row. The move folds into the
+// add or multiply-add that uses it, where a uniform LDS read takes LDS time.
+template <int N>
+__device__ __forceinline__ float row_bcast(float x) {
+  return __int_as_float(
+      __builtin_amdgcn_mov_dpp(__float_as_int(x), kDppRowNewBcast + N, 0xF, 0xF, true));
+}
+template <int N>
+__device__ __forceinline__ int row_bcast(int x) {
+  return __builtin_amdgcn_mov_dpp(x, kDppRowNewBcast + N, 0xF, 0xF, true);
 }
 
 // Inclusive prefix sum within aligned groups of W = 16, 32 or 64 lanes, FP32,

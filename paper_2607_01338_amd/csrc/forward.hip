@@ -48,11 +48,15 @@ namespace iris {
 // Fields of the per-cell LDS table. The table of a sightline is field-major
 // (field f of cell i at f * W + i): each lane writes its cell's fields to
 // consecutive words, and the march reads one field of four cells at once.
-// The profile argument of lane sl in pass q is t = (sl + W q) A + c0.
-enum : int { kRowG = 0, kRowA, kRowC0, kRowLk, kRowKstart, kRowPacked, kRowEmPex,
-             kRowH, kRowKd, kRowEk };
-// Fields per cell: the source-function split (GEN) adds three.
-__host__ __device__ constexpr int fwd_row_fields(bool general) { return general ? 10 : 7; }
+// The profile argument of lane sl in pass q is t = (sl + W q + m) A. The
+// window's first channel is held as a byte offset into the channel state.
+enum : int { kRowG = 0, kRowA, kRowM, kRowLk, kRowKstart, kRowPacked = kRowKstart, kRowH, kRowKd,
+             kRowEkm1 };
+// Fields per cell: the source-function split (GEN) adds three, checkpoints one
+// (e^{-Pex}, the last).
+__host__ __device__ constexpr int fwd_row_fields(bool general, bool ckpt) {
+  return (general ? 8 : 5) + (ckpt ? 1 : 0);
+}
 
 // Scaled-state range of the march: a chunk is cut before the first cell
 // whose dust depth above the current base exceeds kCutTau, and the base is
@@ -73,8 +77,8 @@ __host__ __device__ inline int fwd_state_stride(int n_chan, int groups) {
 // sightline, each broadcast to its lanes) sit in different LDS banks.
 constexpr int kTblSkew = 4;
 // Floats of LDS per wavefront: G channel states plus the 64-row cell table.
-__host__ __device__ inline int fwd_wave_floats(int n_chan, int groups, bool general) {
-  return groups * fwd_state_stride(n_chan, groups) + 64 * fwd_row_fields(general) +
+__host__ __device__ inline int fwd_wave_floats(int n_chan, int groups, bool general, bool ckpt) {
+  return groups * fwd_state_stride(n_chan, groups) + 64 * fwd_row_fields(general, ckpt) +
          groups * kTblSkew;
 }
 
@@ -100,7 +104,8 @@ struct LoaderMaker<DynLoader> {
 template <typename LoaderT, bool GEN, int G, bool CKPT>
 __device__ __forceinline__ void fwd_wave(const FwdParams& P, int64_t pix0, float* lw) {
   constexpr int W = 64 / G;
-  constexpr int TF = fwd_row_fields(GEN);
+  constexpr int TF = fwd_row_fields(GEN, CKPT);
+  constexpr int kRowEmPex = TF - 1;  // checkpoints only
   const int lane = threadIdx.x & 63;
   const int sub = lane / W, sl = lane % W;
   const int64_t pix = pix0 + sub;
@@ -132,14 +137,23 @@ __device__ __forceinline__ void fwd_wave(const FwdParams& P, int64_t pix0, float
   // The fields of the next chunk are loaded while this chunk marches, for a
   // chunk that starts where this one would end uncut (s0 + W); a chunk cut
   // short by the dust depth reloads its successor.
+  // Fields below 4 GiB are addressed by 32-bit byte offsets (`narrow`, the same
+  // for every lane), advanced by addition.
   int s0 = 0;
   int s_pre = 0;
-  typename LoaderT::Raw pre = load.fetch((int64_t)sl * P.at.los, live && sl < P.n_los);
+  const bool narrow = P.narrow != 0;
+  const uint32_t los_bytes = (uint32_t)P.at.los * load.elem_bytes();
+  uint32_t cell_at = (uint32_t)P.at.base(pixc) * load.elem_bytes() + (uint32_t)sl * los_bytes;
+  auto fetch = [&](int s, uint32_t at, bool in) {
+    return narrow ? load.fetch_at(at, in)
+                  : load.fetch_at((P.at.base(pixc) + (int64_t)s * P.at.los) * load.elem_bytes(),
+                                  in);
+  };
+  typename LoaderT::Raw pre = fetch(sl, cell_at, live && sl < P.n_los);
   while (s0 < P.n_los) {
     const int s = s0 + sl;
     const bool valid = live && s < P.n_los;
-    const CellIn in =
-        load.decode(s0 == s_pre ? pre : load.fetch((int64_t)s * P.at.los, valid), valid);
+    const CellIn in = load.decode(s0 == s_pre ? pre : fetch(s, cell_at, valid), valid);
     const CellOut o = cell_setup<GEN>(c, in, valid, true);
 
     // Dust prefix: FP32 scan inside the chunk (at most W terms) on top of Pb.
@@ -149,7 +163,7 @@ __device__ __forceinline__ void fwd_wave(const FwdParams& P, int64_t pix0, float
     // The entry scale of a cell is its predecessor's exit scale, bit for bit.
     const float Pup = lane_up1(Pin);
     const float Pex = sl == 0 ? Pb : Pup;
-    const uint64_t over = __ballot(valid && Pin > kCutTau);
+    const uint64_t over = __builtin_amdgcn_ballot_w64(valid && Pin > kCutTau);
     int nv = min(W, P.n_los - s0);
     if (over) {
 #pragma unroll
@@ -164,7 +178,7 @@ __device__ __forceinline__ void fwd_wave(const FwdParams& P, int64_t pix0, float
     const float eex = ex2(Pex * kLog2e);  // e^{P_{n-1} - base}
     const float ein = ex2(Pin * kLog2e);  // e^{P_n - base}
     // Dust emission entering the continuum, scaled: J_D (1 - e^{-kD}) e^{P_n - base}.
-    const float om = __any(act && o.kD >= 0.25f) ? one_minus_exp_neg(o.kD)
+    const float om = __builtin_amdgcn_ballot_w64(act && o.kD >= 0.25f) ? one_minus_exp_neg(o.kD)
                                                  : one_minus_exp_neg_small(o.kD);
     const float w = act ? o.JD * om * ein : 0.f;
     const float Sin = group_scan_dpp<W>(w);
@@ -193,58 +207,79 @@ __device__ __forceinline__ void fwd_wave(const FwdParams& P, int64_t pix0, float
     // Table row of this lane's cell. A cell without a line gets g = 0 and
     // an optical-depth exponent that flushes to zero, so that a pass over it
     // leaves the state bit-identical.
-    const int np = act ? window_passes(o.nwin, W) : 0;
+    const bool np = act && o.nwin > 0;
     // The lean march needs one pass per cell (the general loop's pass bounds
     // across groups are not needed then).
-    const bool lean = !__any(np > 1);
+    const bool lean = __builtin_amdgcn_ballot_w64(act && o.nwin > W) == 0;
+    // Cells (bit i: cell i of any sightline) whose line is too deep for the
+    // faint step, which a group of four cells takes where none is: one cell in
+    // twenty of the CMZ cube, neighbours together.
+    uint64_t deep = __builtin_amdgcn_ballot_w64(np && o.kL > kFaintTau);
+    if (G == 4) deep |= deep >> 16;
+    if (G >= 2) deep |= deep >> 32;
 
     {
-      int packed = o.kstart | (np << 13);
-      if (!lean) {
-        const int npmax = cross_group_max<W>(np);
-        const int npmin = cross_group_min<W>(np);
-        packed |= (npmax << 21) | ((npmin == npmax) << 29);
-      }
       float* r = tbl + sl;
       r[kRowG * W] = np ? Gn : 0.f;
       r[kRowA * W] = o.A;
-      r[kRowC0 * W] = o.c0;
+      r[kRowM * W] = np ? o.m : 0.f;  // a velocity beyond every grid has none
       r[kRowLk * W] = np ? o.lk : -256.f;
-      r[kRowKstart * W] = __int_as_float(np ? o.kstart : 0);
-      r[kRowPacked * W] = __int_as_float(packed);
+      if (lean) {
+        r[kRowKstart * W] = __int_as_float(np ? 4 * o.kstart : 0);
+      } else {
+        // The first channel, the passes of this cell (bits 13..20), the most over
+        // the groups (21..28) and whether the groups agree (29).
+        const int passes = act ? window_passes(o.nwin, W) : 0;
+        const int npmax = cross_group_max<W>(passes);
+        const int npmin = cross_group_min<W>(passes);
+        r[kRowPacked * W] = __int_as_float(o.kstart | (passes << 13) | (npmax << 21) |
+                                           ((npmin == npmax) << 29));
+      }
       if (CKPT) r[kRowEmPex * W] = ex2(-Pex * kLog2e);
       if (GEN) {
         r[kRowH * W] = (float)((double)(o.JL - o.JD) * (double)eex);
         r[kRowKd * W] = o.kD;
-        r[kRowEk * W] = ex2(o.kD * kLog2e);
+        // e^{kD} - 1, by its series where that is a small difference.
+        r[kRowEkm1 * W] = o.kD < 0.25f ? -one_minus_exp_neg_small(-o.kD)
+                                       : ex2(o.kD * kLog2e) - 1.f;
       }
     }
     wave_order();
 
     s_pre = s0 + W;
-    pre = load.fetch((int64_t)(s_pre + sl) * P.at.los, live && s_pre + sl < P.n_los);
+    pre = fetch(s_pre + sl, cell_at + (uint32_t)W * los_bytes, live && s_pre + sl < P.n_los);
+    cell_at += (uint32_t)nv * los_bytes;
 
     // One channel's step: the formal step of the shared source function, and
     // with separate line and dust source functions (GEN) the term of the
-    // line source's own part, beta h (e^{-kD} - e^{-tau_L}) scaled, beta the
-    // line's share of the total depth.
-    auto gen_step = [&](float ps, float g, float x, float h, float kd, float ek) {
-      float nw = formal_line_step(ps, g, x);
+    // line source's own part, beta h (e^{kD} - e^{-tau_L}) scaled, beta the
+    // line's share of the total depth. FAINT: the step without an exponential.
+    auto step = [&](auto faint, float ps, float g, float x, float h, float kd, float ekm1) {
+      float om, nw;
+      if constexpr (decltype(faint)::value) {
+        const float q = faint_absorbed_over_x(x);
+        nw = fmaf(-((ps + g) * x), q, ps);
+        om = x * q;
+      } else {
+        om = line_absorbed(x);
+        nw = fmaf(-(ps + g), om, ps);
+      }
       if (GEN) {
-        const float E = ex2(-x);  // e^{-tau_L}
         const float tL = x * kLn2;
         const float beta = tL * __builtin_amdgcn_rcpf(fmaxf(tL + kd, 1e-30f));
-        nw = fmaf(beta * h, ek - E, nw);
+        nw = fmaf(beta * h, ekm1 + om, nw);
       }
       return nw;
     };
+    using Faint = std::integral_constant<bool, true>;
+    using Any = std::integral_constant<bool, false>;
     if (lean) {
       // Lean march: every window fits one W-lane pass. Per cell and lane:
-      // profile argument, two exponentials (the line depth and the step,
-      // whose series form serves below x = kSeriesX), one LDS
-      // read-modify-write. Four cells at a time: their table rows and
-      // exponentials do not depend on the state, so they are computed ahead of
-      // the four updates.
+      // profile argument, the exponential of the line depth, the step (in
+      // groups with a deep line another exponential, whose series form serves
+      // below x = kSeriesX), one LDS read-modify-write. Four cells at a time:
+      // their table rows and exponentials do not depend on the state, so they
+      // are computed ahead of the four updates.
       // Checkpoints (line excess entering cell s0 + i, for the adjoint) are
       // written before the cell that starts a checkpoint interval; a group of
       // four with such a cell after its first goes one cell at a time.
@@ -257,48 +292,68 @@ __device__ __forceinline__ void fwd_wave(const FwdParams& P, int64_t pix0, float
         }
       };
       int i = 0;
-      for (; i + 4 <= nv; i += 4) {
-        if (CKPT) {
-          if (((s0 + i) & (K - 1)) > K - 4) break;
-          checkpoint(i);
-        }
-        const float4 g = *(const float4*)(tbl + kRowG * W + i);
-        const float4 A = *(const float4*)(tbl + kRowA * W + i);
-        const float4 c0 = *(const float4*)(tbl + kRowC0 * W + i);
-        const float4 lk = *(const float4*)(tbl + kRowLk * W + i);
-        const int4 off = *(const int4*)(tbl + kRowKstart * W + i);
-        const float x0 = ex2(fmaf(-fmaf(slf, A.x, c0.x), fmaf(slf, A.x, c0.x), lk.x));
-        const float x1 = ex2(fmaf(-fmaf(slf, A.y, c0.y), fmaf(slf, A.y, c0.y), lk.y));
-        const float x2 = ex2(fmaf(-fmaf(slf, A.z, c0.z), fmaf(slf, A.z, c0.z), lk.z));
-        const float x3 = ex2(fmaf(-fmaf(slf, A.w, c0.w), fmaf(slf, A.w, c0.w), lk.w));
-        float4 h = make_float4(0.f, 0.f, 0.f, 0.f), kd = h, ek = h;
+      bool whole = true;  // every group of four so far was taken whole
+#pragma unroll
+      for (int j = 0; j < W / 16; ++j) {
+        // The fields that an add or multiply-add can take by a row broadcast
+        // are held per lane, cell 16 j + lane % 16 of the sightline in every
+        // row; lk comes as one 16-byte read per four cells. (With all five
+        // fields read from LDS, LDS was as busy as the VALU.)
+        const float* tj = tbl + 16 * j + (lane & 15);
+        const float gj = tj[kRowG * W], Aj = tj[kRowA * W], mj = tj[kRowM * W];
+        const int oj = __float_as_int(tj[kRowKstart * W]);
+        float hj = 0.f, kdj = 0.f, ej = 0.f;
         if (GEN) {
-          h = *(const float4*)(tbl + kRowH * W + i);
-          kd = *(const float4*)(tbl + kRowKd * W + i);
-          ek = *(const float4*)(tbl + kRowEk * W + i);
+          hj = tj[kRowH * W];
+          kdj = tj[kRowKd * W];
+          ej = tj[kRowEkm1 * W];
         }
-        float* p0 = psi + off.x + sl;
-        *p0 = gen_step(*p0, g.x, x0, h.x, kd.x, ek.x);
-        wave_order();
-        float* p1 = psi + off.y + sl;
-        *p1 = gen_step(*p1, g.y, x1, h.y, kd.y, ek.y);
-        wave_order();
-        float* p2 = psi + off.z + sl;
-        *p2 = gen_step(*p2, g.z, x2, h.z, kd.z, ek.z);
-        wave_order();
-        float* p3 = psi + off.w + sl;
-        *p3 = gen_step(*p3, g.w, x3, h.w, kd.w, ek.w);
-        wave_order();
+        auto four = [&](auto quad, auto faint) {
+          constexpr int n0 = 4 * decltype(quad)::value;
+          const float4 lk = *(const float4*)(tbl + kRowLk * W + 16 * j + n0);
+          const float t0 = (slf + row_bcast<n0>(mj)) * row_bcast<n0>(Aj);
+          const float t1 = (slf + row_bcast<n0 + 1>(mj)) * row_bcast<n0 + 1>(Aj);
+          const float t2 = (slf + row_bcast<n0 + 2>(mj)) * row_bcast<n0 + 2>(Aj);
+          const float t3 = (slf + row_bcast<n0 + 3>(mj)) * row_bcast<n0 + 3>(Aj);
+          const float x0 = ex2(fmaf(-t0, t0, lk.x)), x1 = ex2(fmaf(-t1, t1, lk.y));
+          const float x2 = ex2(fmaf(-t2, t2, lk.z)), x3 = ex2(fmaf(-t3, t3, lk.w));
+          auto one = [&](auto cell, float x) {
+            constexpr int n = decltype(cell)::value;
+            float* p = (float*)((char*)(psi + sl) + row_bcast<n>(oj));
+            *p = step(faint, *p, row_bcast<n>(gj), x, row_bcast<n>(hj), row_bcast<n>(kdj),
+                      row_bcast<n>(ej));
+            wave_order();
+          };
+          one(std::integral_constant<int, n0>{}, x0);
+          one(std::integral_constant<int, n0 + 1>{}, x1);
+          one(std::integral_constant<int, n0 + 2>{}, x2);
+          one(std::integral_constant<int, n0 + 3>{}, x3);
+        };
+        auto quad = [&](auto q) {
+          if (!whole) return;
+          if (i + 4 > nv || (CKPT && ((s0 + i) & (K - 1)) > K - 4)) {
+            whole = false;
+            return;
+          }
+          if (CKPT) checkpoint(i);
+          if ((deep >> i) & 15) four(q, Any{});
+          else four(q, Faint{});
+          i += 4;
+        };
+        quad(std::integral_constant<int, 0>{});
+        quad(std::integral_constant<int, 1>{});
+        quad(std::integral_constant<int, 2>{});
+        quad(std::integral_constant<int, 3>{});
       }
       for (; i < nv; ++i) {
         checkpoint(i);
         const float g = tbl[kRowG * W + i], A = tbl[kRowA * W + i];
-        const float c0 = tbl[kRowC0 * W + i], lk = tbl[kRowLk * W + i];
-        const float t = fmaf(slf, A, c0);
-        float* pp = psi + __float_as_int(tbl[kRowKstart * W + i]) + sl;
-        *pp = GEN ? gen_step(*pp, g, ex2(fmaf(-t, t, lk)), tbl[kRowH * W + i],
-                             tbl[kRowKd * W + i], tbl[kRowEk * W + i])
-                  : gen_step(*pp, g, ex2(fmaf(-t, t, lk)), 0.f, 0.f, 0.f);
+        const float m = tbl[kRowM * W + i], lk = tbl[kRowLk * W + i];
+        const float t = (slf + m) * A;
+        float* pp = (float*)((char*)(psi + sl) + __float_as_int(tbl[kRowKstart * W + i]));
+        *pp = GEN ? step(Any{}, *pp, g, ex2(fmaf(-t, t, lk)), tbl[kRowH * W + i],
+                             tbl[kRowKd * W + i], tbl[kRowEkm1 * W + i])
+                  : step(Any{}, *pp, g, ex2(fmaf(-t, t, lk)), 0.f, 0.f, 0.f);
         wave_order();
       }
     } else {
@@ -315,19 +370,19 @@ __device__ __forceinline__ void fwd_wave(const FwdParams& P, int64_t pix0, float
         const int npm = (pku >> 21) & 0xFF;
         if (npm == 0) continue;
         const int npo = (pk >> 13) & 0xFF;
-        const float g = r[kRowG * W], A = r[kRowA * W], c0 = r[kRowC0 * W], lk = r[kRowLk * W];
-        float h = 0.f, kd = 0.f, ek = 0.f;
+        const float g = r[kRowG * W], A = r[kRowA * W], m = r[kRowM * W], lk = r[kRowLk * W];
+        float h = 0.f, kd = 0.f, ekm1 = 0.f;
         if (GEN) {
           h = r[kRowH * W];
           kd = r[kRowKd * W];
-          ek = r[kRowEk * W];
+          ekm1 = r[kRowEkm1 * W];
         }
         float* pp = psi + (pk & 0x1FFF) + sl;
         for (int q = 0; q < npm; ++q) {
           if (q < npo) {
-            const float t = fmaf(slf + (float)(W * q), A, c0);
+            const float t = (slf + (float)(W * q) + m) * A;
             const float tl = ex2(fmaf(-t, t, lk));  // tau_L * log2(e)
-            pp[W * q] = gen_step(pp[W * q], g, tl, h, kd, ek);
+            pp[W * q] = step(Any{}, pp[W * q], g, tl, h, kd, ekm1);
           }
         }
         wave_order();
@@ -341,7 +396,7 @@ __device__ __forceinline__ void fwd_wave(const FwdParams& P, int64_t pix0, float
     const float Pend = __shfl(Pin, last, 64);
     Ptrue += (double)__shfl(Prel, last, 64);
     const bool clamped = act && c.kD * (float)o.n > kRebaseTau;
-    if (__any(clamped)) Ptrue += (double)group_sum<W>(clamped ? c.kD * (float)o.n - o.kD : 0.f);
+    if (__builtin_amdgcn_ballot_w64(clamped)) Ptrue += (double)group_sum<W>(clamped ? c.kD * (float)o.n - o.kD : 0.f);
     Dcar += (double)__shfl(Sin, last, 64);
     Gcar += (double)__shfl(Gsc, last, 64);
     Jcar = __shfl(o.JD, last, 64);
@@ -374,8 +429,16 @@ __device__ __forceinline__ void fwd_wave(const FwdParams& P, int64_t pix0, float
                    Bout);
 }
 
+// Wavefronts per SIMD the registers leave room for (LDS may hold fewer: five at
+// 800 channels and two sightlines per wavefront). The march alternates chains
+// of LDS read-modify-writes with vector work, and with four it was waiting: the
+// 512 x 512 x 128 x 800-channel cube took 645 us at four, 600 at five; the bf16
+// 150 x 203 x 95 cube with 603 marched velocities 78 and 73 us at six.
+template <bool GEN, bool CKPT>
+constexpr int fwd_waves() { return GEN || CKPT ? 5 : 6; }
+
 template <typename FT, bool GEN, int G, bool CKPT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void fwd_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(fwd_waves<GEN, CKPT>()))) void fwd_kernel(
     const FwdParams P) {
   extern __shared__ float lds[];
   const int wave = threadIdx.x >> 6;
@@ -383,20 +446,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
   const int64_t pix0 = ((int64_t)tile * kWavesPerBlock + wave) * G;
   if (pix0 >= P.n_pix) return;  // whole wavefront
   fwd_wave<Loader<FT>, GEN, G, CKPT>(P, pix0,
-                                      lds + (size_t)wave * fwd_wave_floats(P.c.n_chan, G, GEN));
+                                      lds + (size_t)wave * fwd_wave_floats(P.c.n_chan, G, GEN, CKPT));
 }
 
 int fwd_state_floats(int n_chan, int groups) { return fwd_state_stride(n_chan, groups); }
 
-size_t fwd_lds_bytes(int n_chan, int groups, bool general) {
-  return (size_t)kWavesPerBlock * fwd_wave_floats(n_chan, groups, general) * sizeof(float);
+size_t fwd_lds_bytes(int n_chan, int groups, bool general, bool ckpt) {
+  return (size_t)kWavesPerBlock * fwd_wave_floats(n_chan, groups, general, ckpt) * sizeof(float);
 }
 
 template <typename FT, int G>
 static int launch_g(const FwdParams& p, void* stream) {
   const int64_t waves = (p.n_pix + G - 1) / G;
   const int blocks = (int)((waves + kWavesPerBlock - 1) / kWavesPerBlock);
-  const size_t lds = fwd_lds_bytes(p.c.n_chan, G, p.c.general != 0);
+  const size_t lds = fwd_lds_bytes(p.c.n_chan, G, p.c.general != 0, p.ckpt_K > 0);
   const dim3 grid(blocks), block(64 * kWavesPerBlock);
   const hipStream_t st = (hipStream_t)stream;
   const bool ck = p.ckpt_K > 0;
@@ -436,7 +499,7 @@ int launch_forward(iris_dtype dt, const FwdParams& p, void* stream) {
 // sliced queue (ItemClaim) until it is empty. Storage type, G and the
 // source-function variant are taken per cube at run time.
 template <int G, bool CKPT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void plan_fwd_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void plan_fwd_kernel(
     const PlanFwdParams Q) {
   extern __shared__ float lds[];
   const int wave = threadIdx.x >> 6;

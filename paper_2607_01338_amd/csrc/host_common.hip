@@ -346,7 +346,10 @@ int thin_groups(const Folded& c, int n_chan, bool selective) {
 }
 
 bool groups_fit(int n_chan, int groups, bool general) {
-  return fwd_lds_bytes(n_chan, groups, general) <= 65536;
+  // The channel counts a packing takes do not depend on the checkpoints: two
+  // fields per cell of room beyond the march without them.
+  return fwd_lds_bytes(n_chan, groups, general, false) +
+             (size_t)kWavesPerBlock * 64 * 2 * sizeof(float) <= 65536;
 }
 
 // ---- choice of sightlines per wavefront ------------------------------------
@@ -521,6 +524,8 @@ FwdParams fwd_params(const iris_fields* f, const Geo& g, const iris_channels* ch
   p.ckpt_K = K;
   p.groups = groups;
   p.dtype = (int32_t)f->dtype;
+  // Past the last cell a lane may form the offset of one more chunk of 64 cells.
+  p.narrow = (uint64_t)(g.n_cells + 64 * at.los) * elem_size(f->dtype) < (1ull << 32) ? 1 : 0;
   p.lds_per_wave = fwd_state_floats(ch->n_chan, groups);
   p.ck_state = ck_state;
   p.ck_scal = ck_scal;

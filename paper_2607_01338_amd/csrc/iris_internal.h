@@ -107,6 +107,8 @@ struct FwdParams {
   int32_t lds_per_wave;   // floats of channel state per sightline (multiple of 4)
   int32_t groups;         // sightlines per wavefront: 1, 2 or 4
   int32_t dtype;          // iris_dtype of the fields (used by batched launches)
+  int32_t narrow;         // 1: every byte offset into a field fits 32 bits
+  int32_t pad_;
   float* ck_state;        // [n_ck][n_pix][n_chan] line excess entering cell ck*K
   double* ck_scal;        // [n_ck][n_pix][kCkScal]: see kCk* below
 };
@@ -216,7 +218,7 @@ int launch_forward(iris_dtype dt, const FwdParams& p, void* stream);
 int launch_smooth(iris_dtype dt, const FwdParams& p, void* stream);
 int smooth_max_channels();
 int fwd_state_floats(int n_chan, int groups);
-size_t fwd_lds_bytes(int n_chan, int groups, bool general);
+size_t fwd_lds_bytes(int n_chan, int groups, bool general, bool ckpt);
 int launch_plan_forward(const PlanFwdParams& q, int groups, bool ckpt, int blocks, void* stream);
 int plan_forward_occupancy(int wave_floats, int groups, bool ckpt);
 int launch_adjoint(iris_dtype dt, const AdjParams& p, void* stream);

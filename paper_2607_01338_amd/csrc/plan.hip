@@ -449,7 +449,7 @@ iris_status build_plan(const iris_cube* cubes, int n, const iris_line* L, int fl
     const int c = P->groups[i] == 1 ? 0 : P->groups[i] == 2 ? 1 : 2;
     fwd_wave_floats[c] = std::max<int>(
         fwd_wave_floats[c],
-        (int)(fwd_lds_bytes(mch[i].n_chan, P->groups[i], folded[i].general != 0) /
+        (int)(fwd_lds_bytes(mch[i].n_chan, P->groups[i], folded[i].general != 0, P->K > 0) /
               (sizeof(float) * kWavesPerBlock)));
     samples += g.n_cells * cb.channels.n_chan;
     if (adj) {

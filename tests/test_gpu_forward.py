@@ -331,3 +331,38 @@ def test_check_fields_counts_unusable_values(dt):
     with pytest.raises(rt.IrisError) as e:
         rt.iris_rt_check_fields(*args, axis=2, cell_cm=cube.cell_cm)
     assert e.value.status == 5 and "6 field values" in str(e.value)
+
+
+@pytest.mark.parametrize("groups", [1, 2, 4])
+@pytest.mark.parametrize("scale", [1.0, 40.0])
+def test_faint_and_deep_groups_of_cells(scale, groups, monkeypatch):
+    # Line depths on both sides of the faint step's bound within groups of four
+    # cells, chunk remainders, with a dust temperature field and without; at
+    # 40 times the abundance most groups are deep.
+    monkeypatch.setenv("IRIS_RT_SIGHTLINES_PER_WAVE", str(groups))
+    for t_dust in (False, True):
+        cube = W.make_cube((3, 7, 85), 2, W.Channels(70, -17.5, 0.5), seed=80, v_rms_kms=5.0,
+                           t_dust=t_dust)
+        cube.x_tracer[...] *= scale
+        say(f"[fwd] faint and deep groups, scale {scale}, G = {groups}, t_dust {t_dust}")
+        dev = to_device(cube, "f32")
+        res = gpu_forward(cube, dev)
+        ref = oracle.forward(problem(cube, dequantised(dev)), W.LINE_13CO_21)
+        for k in "TCDLB":
+            e = M.err_inf(res[k].double().cpu().numpy(), ref[k])
+            assert e <= TOL_FWD, (k, e)
+
+
+def test_temperatures_outside_the_tables():
+    # Below 1 K and above 65536 K the level and source functions are direct.
+    cube = W.make_cube((2, 5, 70), 2, W.Channels(64, -16.0, 0.5), seed=81, v_rms_kms=4.0)
+    t = np.geomspace(0.3, 3e5, cube.t_kin.size).reshape(cube.t_kin.shape)
+    cube.t_kin[...] = t
+    say("[fwd] temperatures from 0.3 to 3e5 K")
+    dev = to_device(cube, "f32")
+    line = line_dict(t_inf_k=1e6)
+    res = gpu_forward(cube, dev, line)
+    ref = oracle.forward(problem(cube, dequantised(dev)), line)
+    for k in "TCDLB":
+        e = M.err_inf(res[k].double().cpu().numpy(), ref[k])
+        assert e <= TOL_FWD, (k, e)
