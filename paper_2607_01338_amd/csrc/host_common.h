@@ -19,6 +19,10 @@ int launch_thin(const FwdParams& p, bool smooth, bool selective, int groups, voi
                 void* stream);
 size_t thin_lds_bytes(int n_chan, int groups, bool selective);
 size_t thin_static_lds_bytes();
+// Terms of the narrow-channel series that the channel width allows (0: wide
+// channels, the erfc pieces), and LDS of that kernel's workgroup.
+int thin_series_order(const Folded& c);
+size_t thin_series_lds_bytes(int n_chan, int groups, bool selective, int order);
 // Reverse mode of optically thin transfer (thin.hip); LDS of its workgroup.
 int launch_thin_adjoint(const AdjParams& p, bool smooth, int groups, void* table, void* stream);
 size_t thin_adj_lds_bytes(int n_chan, int groups);

@@ -335,14 +335,24 @@ int thin_groups(const Folded& c, int n_chan, bool selective) {
   const double b100 = std::sqrt((double)c.bT * 100.0 + (double)c.bt2);
   const double width = 2 * std::sqrt(std::log(1.0 / kWindowEps)) * b100 * c.inv_dv + 3.0;
   int groups = width <= 15.0 ? 4 : width <= 31.0 ? 2 : 1;
+  const int order = thin_series_order(c);
+  if (order) {
+    // All the lanes of a pass carry a channel: at most floor(2 hw + 1) + 1 of
+    // them meet a window of half-width hw.
+    const double most = std::floor(width - 2.0) + 1.0;
+    groups = most <= 16.0 ? 4 : most <= 32.0 ? 2 : 1;
+  }
   if (const char* e = std::getenv("IRIS_RT_THIN_GROUPS")) {
     if (std::strcmp(e, "1") == 0) groups = 1;
     if (std::strcmp(e, "2") == 0) groups = 2;
     if (std::strcmp(e, "4") == 0) groups = 4;
   }
-  while (groups > 1 && thin_lds_bytes(n_chan, groups, selective) + thin_static_lds_bytes() > 65536)
-    groups = 1;
-  return thin_lds_bytes(n_chan, groups, selective) + thin_static_lds_bytes() > 65536 ? 0 : groups;
+  auto fits = [&](int g) {
+    return thin_lds_bytes(n_chan, g, selective) + thin_static_lds_bytes() <= 65536 &&
+           (!order || thin_series_lds_bytes(n_chan, g, selective, order) <= 65536);
+  };
+  while (groups > 1 && !fits(groups)) groups = 1;
+  return fits(groups) ? groups : 0;
 }
 
 bool groups_fit(int n_chan, int groups, bool general) {

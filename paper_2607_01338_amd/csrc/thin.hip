@@ -41,6 +41,9 @@
 #include "cell_setup.h"
 #include "epilogue.h"
 #include "erfc_table.h"
+#include "host_common.h"
+
+#include <cmath>
 
 namespace iris {
 
@@ -310,6 +313,283 @@ __global__ __launch_bounds__(256) void thin_kernel(const FwdParams P, int smooth
     write_outputs<W>(c, P.out, pix, psi, sl, c.out_scale, (float)(c.J_bg + Dsum), Dsum, c.J_bg);
 }
 
+// --- narrow channels -----------------------------------------------------------
+//
+// Where a channel is narrow against the line, the channel mean needs no erfc
+// table. With h half a channel's width and x a channel's centre, both in
+// Doppler widths, y = x^2,
+//   (1/2h) int_{x-h}^{x+h} e^{-t^2} dt = e^{-y} F(y),
+//   F = sum_j (4 h^2 y)^j / (2j)! mu_j,  mu_j = int_0^1 s^{2j} e^{-h^2 s^2} ds,
+// a series of positive terms (no cancellation, tails keep their relative
+// accuracy), taken to j = M. Its relative error is largest at the window's
+// edge, (2 h x)^{2M+2} / (2M+2)! / (2M+3) / F: at x = 4.55 + h, 4e-6 of a profile
+// of 1e-9 for h = 0.18 and M = 4, 2e-6 for h = 0.36 and M = 7. The turbulent
+// broadening bounds h on the host: b >= sqrt(2) sigma whatever T is.
+constexpr double kSeriesH4 = 0.18, kSeriesH7 = 0.36;
+
+int thin_series_order(const Folded& c) {
+  const double h = 0.5 * c.dv / std::sqrt((double)c.bt2);  // inf without turbulence
+  return h <= kSeriesH4 ? 4 : h <= kSeriesH7 ? 7 : 0;
+}
+
+constexpr float inv_factorial(int n) {
+  double f = 1.0;
+  for (int i = 2; i <= n; ++i) f *= i;
+  return (float)(1.0 / f);
+}
+
+// Coefficients of F in y' = y log2 e for a cell with profile scale A
+// (x' = A per channel, h = A / (2 sqrt(log2 e))), times `amp`.
+template <int M>
+__device__ __forceinline__ void series_coeffs(float A, float amp, float (&cf)[M + 1]) {
+  const float A2 = A * A;
+  const float h2 = A2 * (0.25f / kLog2e);
+  const float kappa = A2 * (1.f / (kLog2e * kLog2e));  // 4 h^2 y = kappa y'
+  float p = amp;
+#pragma unroll
+  for (int j = 0; j <= M; ++j) {
+    // mu_j = sum_i (-h^2)^i / (i! (2(i + j) + 1)); h^2 < 0.13: six terms.
+    float mu = 1.f / (120.f * (float)(2 * j + 11));
+    mu = fmaf(-h2, mu, 1.f / (24.f * (float)(2 * j + 9)));
+    mu = fmaf(-h2, mu, 1.f / (6.f * (float)(2 * j + 7)));
+    mu = fmaf(-h2, mu, 1.f / (2.f * (float)(2 * j + 5)));
+    mu = fmaf(-h2, mu, 1.f / (float)(2 * j + 3));
+    mu = fmaf(-h2, mu, 1.f / (float)(2 * j + 1));
+    cf[j] = p * mu;
+    p *= kappa * (1.f / (float)((2 * j + 1) * (2 * j + 2)));
+  }
+}
+
+// Cell table of a sightline: four coefficients per cell as one 16-byte row, and
+// field-major the fields taken by row broadcasts (x' = (lane + m) A, the first
+// channel's byte offset, the higher coefficients, the selective floor).
+enum : int { kTsM = 0, kTsA, kTsOff, kTsC4 };
+__host__ __device__ constexpr int ts_fields(int M, bool sel) { return 3 + (M - 3) + (sel ? 1 : 0); }
+constexpr int kTsSkew = 4;
+__host__ __device__ inline int ts_wave_floats(int n_chan, int groups, bool sel, int M) {
+  return 64 * (4 + ts_fields(M, sel)) + groups * kTsSkew + groups * thin_state_stride(n_chan, groups);
+}
+
+// The thin and selectively thin forward for narrow channels: packing, windows
+// and the selective step as in thin_kernel, the lane's channel evaluated at its
+// centre (all W lanes of a pass carry a channel). Per window sample one
+// exponential, about ten vector instructions and a quarter of a 16-byte LDS
+// read beside the read-modify-write of the sum, where the table needs a 16-byte
+// gather and 25 instructions. 256 x 256 x 128 cells, 800 channels of 0.5 km/s:
+// THIN_TIMES.
+template <bool GEN, int G, bool SEL, int M>
+__global__ __launch_bounds__(256) void thin_series_kernel(const FwdParams P, int smooth) {
+  constexpr int W = 64 / G;
+  constexpr int NF = ts_fields(M, SEL);
+  constexpr int kFloor = NF - 1;  // selective
+  extern __shared__ float lds[];
+  const int wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int sub = lane / W, sl = lane % W;
+  const int tile = xcd_tile((int)blockIdx.x, (int)gridDim.x);
+  const int64_t pix0 = ((int64_t)tile * kWavesPerBlock + wave) * G;
+  if (pix0 >= P.n_pix) return;  // whole wavefront
+  const int64_t pix = pix0 + sub;
+  const bool live = pix < P.n_pix;
+  const Folded& c = P.c;
+  const int C = c.n_chan;
+  const int stride = thin_state_stride(C, G);
+  float* lw = lds + (size_t)wave * ts_wave_floats(C, G, SEL, M);
+  float* rows = lw + sub * (W * (4 + NF) + kTsSkew);  // [W][4]
+  float* tbl = rows + 4 * W;                          // [NF][W]
+  float* psi = lw + 64 * (4 + NF) + G * kTsSkew + sub * stride;
+  for (int k = sl; k < stride; k += W) psi[k] = 0.f;
+  const int64_t pixc = live ? pix : P.n_pix - 1;
+  const DynLoader load(P.f, P.at.base(pixc), P.dtype);
+  const float slf = (float)sl;
+  double Dsum = 0.0;
+  double Atot = 1.0, Btot = 0.0;  // selective: the continuum map of the sightline so far
+
+  const bool narrow = P.narrow != 0;
+  const uint32_t los_bytes = (uint32_t)P.at.los * load.elem_bytes();
+  uint32_t cell_at = (uint32_t)P.at.base(pixc) * load.elem_bytes() + (uint32_t)sl * los_bytes;
+  auto fetch = [&](int s, uint32_t at) {
+    const bool in = live && s < P.n_los;
+    return narrow ? load.fetch_at(at, in)
+                  : load.fetch_at((P.at.base(pixc) + (int64_t)s * P.at.los) * load.elem_bytes(),
+                                  in);
+  };
+  DynLoader::Raw pre = fetch(sl, cell_at);
+  for (int s0 = 0; s0 < P.n_los; s0 += W) {
+    const int s = s0 + sl;
+    const bool valid = live && s < P.n_los;
+    const CellIn in = load.decode(pre, valid);
+    const CellOut o = cell_setup<GEN>(c, in, valid, true);
+    const float w = valid ? thin_weight(smooth != 0, s, P.n_los) : 0.f;
+    const int nv = min(W, P.n_los - s0);
+    float lw_line = 1.f;
+    float flo = 0.f;
+    if (SEL) {
+      const float tD = valid ? c.kD * (float)o.n : 0.f;
+      const float om = tD >= 0.25f ? one_minus_exp_neg(tD) : one_minus_exp_neg_small(tD);
+      float Am = valid ? 1.f - om : 1.f, Bm = valid ? o.JD * om : 0.f;
+      group_scan_affine<W>(Am, Bm);
+      const float Pin = group_scan_dpp<W>(tD);
+      const int last = sub * W + nv - 1;
+      const float Pend = __shfl(Pin, last, 64);
+      const float Alast = __shfl(Am, last, 64), Blast = __shfl(Bm, last, 64);
+      const float Cn = fmaf(Am, (float)(Atot * c.J_bg + Btot), Bm);
+      const float fD = tD > 1e-4f ? om / tD : 1.f - 0.5f * tD;
+      const float esc = ex2((Pin - Pend) * kLog2e);
+      lw_line = (o.JL - Cn) * fD * esc;
+      flo = -Cn * esc;
+      const float resc = ex2(-Pend * kLog2e);
+      for (int k = sl; k < C; k += W) psi[k] *= resc;
+      Btot = (double)Alast * Btot + (double)Blast;
+      Atot *= (double)Alast;
+    } else {
+      Dsum += (double)group_allsum<W>(w * (c.kD * (float)o.n) * o.JD);
+    }
+    // Channels whose extent meets |v' - v| <= x_w b, clipped to the grid.
+    const double ud = fma(in.v - c.v_lo, c.inv_dv, -0.5);
+    const float u = (float)ud;
+    const float xw = __builtin_amdgcn_sqrtf(c.xw2min + fmaxf(0.f, (o.lk - 0.52876637f) * kLn2));
+    const float hw = xw * kSqrtLog2e * __builtin_amdgcn_rcpf(o.A);
+    const float e0f = fmaxf(ceilf(u - hw - 0.5f), 0.f);
+    const float e1f = fminf(floorf(u + hw + 0.5f), (float)(C - 1));
+    const bool line = w > 0.f && o.kL > 0.f && o.kL >= c.kL_min && e0f <= e1f;
+    const int ne = line ? (int)(e1f - e0f) + 1 : 0;
+    const bool lean = __builtin_amdgcn_ballot_w64(ne > W) == 0;
+    {
+      // A cell without a line adds zero: x' = 0, every coefficient 0.
+      const float A = line ? o.A : 0.f;
+      float cf[M + 1];
+      series_coeffs<M>(A, line ? w * o.kL * (SEL ? lw_line : o.JL) : 0.f, cf);
+      *(float4*)(rows + 4 * sl) = make_float4(cf[0], cf[1], cf[2], cf[3]);
+      float* r = tbl + sl;
+      r[kTsM * W] = line ? (float)((double)e0f - ud) : 0.f;
+      r[kTsA * W] = A;
+      const int e0 = line ? (int)e0f : 0;
+      r[kTsOff * W] = __int_as_float(lean ? 4 * e0 : e0 | (window_passes(ne, W) << 13));
+#pragma unroll
+      for (int j = 4; j <= M; ++j) r[(kTsC4 + j - 4) * W] = cf[j];
+      // A cell without a line leaves the sums alone.
+      if (SEL) r[kFloor * W] = line ? flo : -3.402823466e38f;
+    }
+    wave_order();
+    pre = fetch(s0 + W + sl, cell_at + (uint32_t)W * los_bytes);
+    cell_at += (uint32_t)W * los_bytes;
+
+    if (lean) {
+      // Four cells at a time; cells beyond the sightline carry no line.
+#pragma unroll
+      for (int j = 0; j < W / 16; ++j) {
+        if (16 * j >= nv) break;
+        const float* tj = tbl + 16 * j + (lane & 15);
+        const float mj = tj[kTsM * W], Aj = tj[kTsA * W];
+        const int oj = __float_as_int(tj[kTsOff * W]);
+        float ch[M - 3], fj = 0.f;
+#pragma unroll
+        for (int k = 0; k < M - 3; ++k) ch[k] = tj[(kTsC4 + k) * W];
+        if (SEL) fj = tj[kFloor * W];
+        auto quad = [&](auto q) {
+          constexpr int n0 = 4 * decltype(q)::value;
+          if (16 * j + n0 >= nv) return;
+          float E[4], F[4];
+          auto mean = [&](auto cell) {
+            constexpr int n = decltype(cell)::value;
+            const float x = (slf + row_bcast<n>(mj)) * row_bcast<n>(Aj);
+            const float y = x * x;
+            E[n - n0] = ex2(-y);
+            const float4 cf = *(const float4*)(rows + 4 * (16 * j + n));
+            float f = row_bcast<n>(ch[M - 4]);
+#pragma unroll
+            for (int k = M - 5; k >= 0; --k) f = f * y + row_bcast<n>(ch[k]);
+            f = f * y + cf.w;
+            f = fmaf(f, y, cf.z);
+            f = fmaf(f, y, cf.y);
+            F[n - n0] = fmaf(f, y, cf.x);
+          };
+          auto add = [&](auto cell) {
+            constexpr int n = decltype(cell)::value;
+            float* p = (float*)((char*)(psi + sl) + row_bcast<n>(oj));
+            const float v = fmaf(E[n - n0], F[n - n0], *p);
+            *p = SEL ? fmaxf(v, row_bcast<n>(fj)) : v;
+            wave_order();
+          };
+          mean(std::integral_constant<int, n0>{});
+          mean(std::integral_constant<int, n0 + 1>{});
+          mean(std::integral_constant<int, n0 + 2>{});
+          mean(std::integral_constant<int, n0 + 3>{});
+          add(std::integral_constant<int, n0>{});
+          add(std::integral_constant<int, n0 + 1>{});
+          add(std::integral_constant<int, n0 + 2>{});
+          add(std::integral_constant<int, n0 + 3>{});
+        };
+        quad(std::integral_constant<int, 0>{});
+        quad(std::integral_constant<int, 1>{});
+        quad(std::integral_constant<int, 2>{});
+        quad(std::integral_constant<int, 3>{});
+      }
+    } else {
+      for (int i = 0; i < nv; ++i) {
+        const float* r = tbl + i;
+        const int pk = __float_as_int(r[kTsOff * W]);
+        const int np = pk >> 13, npm = groups_max<G>(np);
+        const float m = r[kTsM * W], A = r[kTsA * W];
+        const float4 cf = *(const float4*)(rows + 4 * i);
+        float* pp = psi + (pk & 0x1FFF) + sl;
+        for (int q = 0; q < npm; ++q) {
+          if (q < np) {
+            const float x = (slf + (float)(W * q) + m) * A;
+            const float y = x * x;
+            float f = r[(kTsC4 + M - 4) * W];
+#pragma unroll
+            for (int k = M - 5; k >= 0; --k) f = fmaf(f, y, r[(kTsC4 + k) * W]);
+            f = fmaf(f, y, cf.w);
+            f = fmaf(f, y, cf.z);
+            f = fmaf(f, y, cf.y);
+            f = fmaf(f, y, cf.x);
+            const float v = fmaf(ex2(-y), f, pp[W * q]);
+            pp[W * q] = SEL ? fmaxf(v, r[kFloor * W]) : v;
+          }
+        }
+        wave_order();
+      }
+    }
+    wave_order();
+  }
+  if (!live) return;
+  if (SEL)
+    write_outputs<W>(c, P.out, pix, psi, sl, c.out_scale, (float)(Atot * c.J_bg + Btot), Btot,
+                     Atot * c.J_bg);
+  else
+    write_outputs<W>(c, P.out, pix, psi, sl, c.out_scale, (float)(c.J_bg + Dsum), Dsum, c.J_bg);
+}
+
+size_t thin_series_lds_bytes(int n_chan, int groups, bool selective, int order) {
+  return (size_t)kWavesPerBlock * ts_wave_floats(n_chan, groups, selective, order) * sizeof(float);
+}
+
+template <int M>
+static int launch_thin_series(const FwdParams& p, int sm, bool sel, int groups, hipStream_t st) {
+  const int64_t waves = (p.n_pix + groups - 1) / groups;
+  const int blocks = (int)((waves + kWavesPerBlock - 1) / kWavesPerBlock);
+  const size_t lds = thin_series_lds_bytes(p.c.n_chan, groups, sel, M);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(64 * kWavesPerBlock), lds, st, p, sm);
+  };
+  auto pick = [&](auto g, auto s) {
+    constexpr int G = decltype(g)::value;
+    constexpr bool S = decltype(s)::value;
+    if (p.c.general) go(thin_series_kernel<true, G, S, M>);
+    else go(thin_series_kernel<false, G, S, M>);
+  };
+  auto with = [&](auto s) {
+    if (groups == 4) pick(std::integral_constant<int, 4>{}, s);
+    else if (groups == 2) pick(std::integral_constant<int, 2>{}, s);
+    else pick(std::integral_constant<int, 1>{}, s);
+  };
+  if (sel) with(std::true_type{});
+  else with(std::false_type{});
+  return (int)hipGetLastError();
+}
+
 // Reverse mode of optically thin transfer ("differentiability modes" in
 // "Synthetic Observation Implementation and Algorithms"). Nothing attenuates,
 // so the loss is linear in each cell's emission and the cells are
@@ -329,14 +609,24 @@ __host__ __device__ inline int thin_adj_wave_floats(int n_chan, int groups) {
   return groups * thin_state_stride(n_chan, groups);
 }
 
-template <bool GEN, int G>
+//
+// Narrow channels (M > 0, thin_series_order) need no table and no exponential
+// at the edges: with E = e^{-x^2} at the channel's centre and w = 4 h^2 x^2,
+//   d = (2/sqrt(pi)) 2h E F,  e^{-x_lo^2} - e^{-x_hi^2} = 4h e^{-h^2} E x S(w),
+//   x_lo e^{-x_lo^2} - x_hi e^{-x_hi^2} = 2h e^{-h^2} E (2 x^2 S(w) - K(w)),
+// S = sum w^j / (2j+1)!, K = sum w^j / (2j)! to j = M: no difference of two
+// nearly equal values, and no 16-byte gather per channel. 256 x 256 x 128
+// cells, 800 channels of 0.5 km/s: ADJ_TIMES.
+template <bool GEN, int G, int M>
 __global__ __launch_bounds__(256) void thin_adj_kernel(const AdjParams P, int smooth,
                                                        const float4* erfc_pieces) {
   constexpr int W = 64 / G;
-  __shared__ float4 etab[kErfcN];
+  __shared__ float4 etab[M ? 1 : kErfcN];
   extern __shared__ float lds[];
-  for (int i = threadIdx.x; i < kErfcN; i += blockDim.x) etab[i] = gload(erfc_pieces + i);
-  __syncthreads();
+  if (!M) {
+    for (int i = threadIdx.x; i < kErfcN; i += blockDim.x) etab[i] = gload(erfc_pieces + i);
+    __syncthreads();
+  }
   const int wave = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
   const int sub = lane / W, sl = lane % W;
@@ -394,24 +684,55 @@ __global__ __launch_bounds__(256) void thin_adj_kernel(const AdjParams P, int sm
     const int ne = line ? (int)e1f - e0 + 1 : 0;
     const float x0 = (fmaf((float)e0 - kc, o.A, -Rt) - 0.5f * o.A) * isl;
     const float dvb = o.A * isl;  // dv / b
-    float x = x0;
-    float H = erfc_tab(etab, fabsf(x)), ex = ex2(-x * x * kLog2e);
     float s1 = 0.f, sv = 0.f, sb = 0.f;
+    if constexpr (M > 0) {
+      const float A = o.A;
+      const float m = (float)((double)e0 - fma(in.v - c.v_lo, c.inv_dv, -0.5));
+      const float kappa = A * A * (1.f / (kLog2e * kLog2e));
+      float cf[M + 1];
+      series_coeffs<M>(A, 1.f, cf);
+      float jm = m;
+#pragma unroll 2
+      for (int j = 0; j < ne; ++j, jm += 1.f) {
+        const float x = jm * A;
+        const float y = x * x;  // x^2 log2 e
+        const float gE = gl[e0 + j] * ex2(-y);
+        const float ws = kappa * y;
+        float F = cf[M], S = inv_factorial(2 * M + 1), K = inv_factorial(2 * M);
+#pragma unroll
+        for (int k = M - 1; k >= 0; --k) {
+          F = fmaf(F, y, cf[k]);
+          S = fmaf(S, ws, inv_factorial(2 * k + 1));
+          K = fmaf(K, ws, inv_factorial(2 * k));
+        }
+        s1 = fmaf(gE, F, s1);
+        sv = fmaf(gE * x, S, sv);
+        sb = fmaf(gE, fmaf((2.f / kLog2e) * y, S, -K), sb);
+      }
+      const float h2 = A * isl;  // 2 h
+      const float eh = ex2(-0.25f * A * A);  // e^{-h^2}
+      s1 *= 1.12837916709551257f * h2;
+      sv *= 2.f * h2 * eh * isl;
+      sb *= h2 * eh;
+    } else {
+      float x = x0;
+      float H = erfc_tab(etab, fabsf(x)), ex = ex2(-x * x * kLog2e);
 #pragma unroll 4
-    for (int j = 0; j < ne; ++j) {
-      const float xn = fmaf((float)(j + 1), dvb, x0);
-      const float Hn = erfc_tab(etab, fabsf(xn));
-      const float exn = ex2(-xn * xn * kLog2e);
-      const float xh = x + dvb;
-      const float dpos = H - Hn;
-      const float d = x >= 0.f ? dpos : (xh < 0.f ? -dpos : 2.f - H - Hn);
-      const float g = gl[e0 + j];
-      s1 = fmaf(g, d, s1);
-      sv = fmaf(g, ex - exn, sv);
-      sb = fmaf(g, fmaf(x, ex, -xn * exn), sb);
-      x = xn;
-      H = Hn;
-      ex = exn;
+      for (int j = 0; j < ne; ++j) {
+        const float xn = fmaf((float)(j + 1), dvb, x0);
+        const float Hn = erfc_tab(etab, fabsf(xn));
+        const float exn = ex2(-xn * xn * kLog2e);
+        const float xh = x + dvb;
+        const float dpos = H - Hn;
+        const float d = x >= 0.f ? dpos : (xh < 0.f ? -dpos : 2.f - H - Hn);
+        const float g = gl[e0 + j];
+        s1 = fmaf(g, d, s1);
+        sv = fmaf(g, ex - exn, sv);
+        sb = fmaf(g, fmaf(x, ex, -xn * exn), sb);
+        x = xn;
+        H = Hn;
+        ex = exn;
+      }
     }
     if (valid) {
       const float4 rs = make_float4(s1, sv, sb, 0.f);
@@ -443,12 +764,12 @@ __global__ __launch_bounds__(256) void thin_adj_kernel(const AdjParams P, int sm
   }
 }
 
-template <bool GEN, int G>
+template <int M, bool GEN, int G>
 static void launch_thin_adj_g(const AdjParams& p, int sm, const float4* tab, hipStream_t st) {
   const int64_t waves = (p.n_pix + G - 1) / G;
   const int blocks = (int)((waves + kWavesPerBlock - 1) / kWavesPerBlock);
   const size_t lds = (size_t)kWavesPerBlock * thin_adj_wave_floats(p.c.n_chan, G) * sizeof(float);
-  hipLaunchKernelGGL((thin_adj_kernel<GEN, G>), dim3(blocks), dim3(64 * kWavesPerBlock), lds, st,
+  hipLaunchKernelGGL((thin_adj_kernel<GEN, G, M>), dim3(blocks), dim3(64 * kWavesPerBlock), lds, st,
                      p, sm, tab);
 }
 
@@ -491,21 +812,32 @@ void launch_erfc_table(void* table, void* stream) {
                      (hipStream_t)stream, (float4*)table);
 }
 
+template <int M>
+static void launch_thin_adj(const AdjParams& p, int sm, int groups, const float4* tab,
+                            hipStream_t st) {
+  if (p.c.general) {
+    if (groups == 4) launch_thin_adj_g<M, true, 4>(p, sm, tab, st);
+    else if (groups == 2) launch_thin_adj_g<M, true, 2>(p, sm, tab, st);
+    else launch_thin_adj_g<M, true, 1>(p, sm, tab, st);
+  } else {
+    if (groups == 4) launch_thin_adj_g<M, false, 4>(p, sm, tab, st);
+    else if (groups == 2) launch_thin_adj_g<M, false, 2>(p, sm, tab, st);
+    else launch_thin_adj_g<M, false, 1>(p, sm, tab, st);
+  }
+}
+
 int launch_thin_adjoint(const AdjParams& p, bool smooth, int groups, void* table, void* stream) {
   if (p.c.n_chan < 1 || p.n_los < 1 || !table || (groups != 1 && groups != 2 && groups != 4))
     return (int)hipErrorInvalidValue;
   const hipStream_t st = (hipStream_t)stream;
   const float4* tab = (const float4*)table;
-  launch_erfc_table(table, stream);
   const int sm = smooth ? 1 : 0;
-  if (p.c.general) {
-    if (groups == 4) launch_thin_adj_g<true, 4>(p, sm, tab, st);
-    else if (groups == 2) launch_thin_adj_g<true, 2>(p, sm, tab, st);
-    else launch_thin_adj_g<true, 1>(p, sm, tab, st);
-  } else {
-    if (groups == 4) launch_thin_adj_g<false, 4>(p, sm, tab, st);
-    else if (groups == 2) launch_thin_adj_g<false, 2>(p, sm, tab, st);
-    else launch_thin_adj_g<false, 1>(p, sm, tab, st);
+  switch (thin_series_order(p.c)) {
+    case 4: launch_thin_adj<4>(p, sm, groups, tab, st); break;
+    case 7: launch_thin_adj<7>(p, sm, groups, tab, st); break;
+    default:
+      launch_erfc_table(table, stream);
+      launch_thin_adj<0>(p, sm, groups, tab, st);
   }
   return (int)hipGetLastError();
 }
@@ -517,8 +849,12 @@ int launch_thin(const FwdParams& p, bool smooth, bool selective, int groups, voi
     return (int)hipErrorInvalidValue;
   const hipStream_t st = (hipStream_t)stream;
   float4* tab = (float4*)table;
-  launch_erfc_table(table, stream);
   const int sm = smooth ? 1 : 0;
+  switch (thin_series_order(p.c)) {
+    case 4: return launch_thin_series<4>(p, sm, selective, groups, st);
+    case 7: return launch_thin_series<7>(p, sm, selective, groups, st);
+  }
+  launch_erfc_table(table, stream);
   if (selective) launch_thin_s<true>(p, sm, groups, tab, st);
   else launch_thin_s<false>(p, sm, groups, tab, st);
   return (int)hipGetLastError();
