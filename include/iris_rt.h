@@ -513,8 +513,7 @@ void iris_levels_destroy(iris_levels* levels);
  * sum; the sky beyond the map is empty (zero padding). An angular beam (the
  * paper's 30 arcsec) is given in pixels by the caller, who knows the pixel's
  * angular size. `out` may be `cube`; the workspace (iris_beam_workspace_bytes)
- * must not overlap either. Two passes along n2 then n1, asynchronous on
- * `stream`. */
+ * must not overlap either. Along n2, then along n1, asynchronous on `stream`. */
 size_t iris_beam_workspace_bytes(int32_t n1, int32_t n2, int32_t n_chan);
 iris_status iris_beam_convolve(const float* cube, float* out, int32_t n1, int32_t n2,
                                int32_t n_chan, double fwhm_pix, void* workspace,

@@ -187,21 +187,33 @@ __global__ __launch_bounds__(512) void beam_fused_kernel(const BeamArgs a, int s
 // Workgroups of the fused kernel: the positions along n2 in equal tiles of at
 // most 64, and as many segments of n1 as stay resident together (four
 // wavefronts per SIMD up to R = 7, two beyond, by registers), none shorter
-// than twice the halo it re-reads.
-template <int R>
-int launch_beam_fused(const BeamArgs& a, hipStream_t st) {
-  if constexpr (R > 1)
-    if (a.R < R) return launch_beam_fused<R - 1>(a, st);
+// than four rows. A row costs a workgroup 0.6 + 0.08 R us on an idle device
+// and the halo's rows as much as the segment's own, so small maps want many
+// short segments (80 x 50 x 127, R = 7: 61 us in segments of 27 rows, 21 us in
+// segments of 4).
+struct BeamSplit {
+  int nw = 0, seg_rows = 0;
+  int64_t cols = 0;
+};
+BeamSplit beam_split(const BeamArgs& a) {
+  BeamSplit s;
   const int64_t tiles = (a.n2 + 63) / 64;
-  const int nw = (int)(((a.n2 + tiles - 1) / tiles + kBeamPerWave - 1) / kBeamPerWave);
-  const int64_t cols = tiles * ((a.C + kBeamCh - 1) / kBeamCh);
-  const int64_t resident = (R <= 7 ? 4096 : 2048) / nw;
-  const int64_t segs = std::max<int64_t>(1, std::min<int64_t>(resident / cols, a.n1 / (4 * R)));
-  const int seg_rows = (int)((a.n1 + segs - 1) / segs);
-  const int n_seg = (int)((a.n1 + seg_rows - 1) / seg_rows);
-  const size_t lds = (size_t)2 * (nw * kBeamPerWave + 2 * R) * kBeamCh * sizeof(float);
-  hipLaunchKernelGGL(beam_fused_kernel<R>, dim3((unsigned)(cols * n_seg)), dim3(64 * nw), lds, st,
-                     a, seg_rows, n_seg);
+  s.nw = (int)(((a.n2 + tiles - 1) / tiles + kBeamPerWave - 1) / kBeamPerWave);
+  s.cols = tiles * ((a.C + kBeamCh - 1) / kBeamCh);
+  const int64_t resident = (a.R <= 7 ? 4096 : 2048) / s.nw;
+  const int64_t segs = std::max<int64_t>(1, std::min<int64_t>(resident / s.cols, a.n1 / 4));
+  s.seg_rows = (int)((a.n1 + segs - 1) / segs);
+  return s;
+}
+
+template <int R>
+int launch_beam_fused(const BeamArgs& a, const BeamSplit& s, hipStream_t st) {
+  if constexpr (R > 1)
+    if (a.R < R) return launch_beam_fused<R - 1>(a, s, st);
+  const int n_seg = (int)((a.n1 + s.seg_rows - 1) / s.seg_rows);
+  const size_t lds = (size_t)2 * (s.nw * kBeamPerWave + 2 * R) * kBeamCh * sizeof(float);
+  hipLaunchKernelGGL(beam_fused_kernel<R>, dim3((unsigned)(s.cols * n_seg)), dim3(64 * s.nw), lds,
+                     st, a, s.seg_rows, n_seg);
   return (int)hipGetLastError();
 }
 
@@ -344,15 +356,23 @@ iris_status iris_beam_convolve(const float* cube, float* out, int32_t n1, int32_
   }
   for (int i = 0; i <= a.R; ++i) a.w[i] = (float)(wd[i] / wsum);
   const hipStream_t st = (hipStream_t)stream;
+  const bool v4 = aligned4(cube, n_chan) && aligned4(out, n_chan) && aligned4(workspace, n_chan);
   // One kernel for both axes up to kBeamFusedRadius (its output rows in reach
   // fill the registers beyond); it reads neighbours of what it writes, so an
-  // output that overlaps the cube takes the two passes.
-  if (a.R <= kBeamFusedRadius && !overlap(cube, out, need)) {
+  // output that overlaps the cube takes the two passes. So do wide beams on
+  // maps that leave it short segments, mostly halo: from R = 7 with rows that
+  // the passes load four channels at a time (148 x 96 x 468, segments of 7
+  // rows at R = 7: 55 us against 50; of 14 at R = 10: 94 against 63), from
+  // R = 8 with others (358 x 56 x 187, 8 rows at R = 10: 77 against 73; 449 x
+  // 138 x 74, 13 rows: 92 against 92; 203 x 70 x 446, 15 rows: 97 against 116).
+  const BeamSplit split = beam_split(a);
+  const bool short_segs = v4 ? a.R >= 7 && 2 * split.seg_rows < 3 * a.R
+                             : a.R >= 8 && split.seg_rows < a.R;
+  if (a.R <= kBeamFusedRadius && !short_segs && !overlap(cube, out, need)) {
     a.in = cube;
     a.out = out;
-    return host::hip_status(launch_beam_fused<kBeamFusedRadius>(a, st), "beam kernel");
+    return host::hip_status(launch_beam_fused<kBeamFusedRadius>(a, split, st), "beam kernel");
   }
-  const bool v4 = aligned4(cube, n_chan) && aligned4(out, n_chan) && aligned4(workspace, n_chan);
   const int V = v4 ? 4 : 1;
   // Work items of a pass: the other axis x runs of kBeamRun positions x columns.
   auto blocks_for = [&](int64_t n_axis, int64_t n_other) {

@@ -49,11 +49,12 @@ def test_beam_in_place_and_unaligned_match():
 
 @pytest.mark.parametrize("shape,fwhm", [((7, 65, 33), 0.5), ((130, 64, 31), 7.06),
                                         ((61, 129, 32), 7.2), ((3, 8, 70), 2.39),
+                                        ((250, 63, 801), 7.06), ((41, 33, 36), 3.94),
                                         ((200, 1, 5), 5.0)])
 def test_beam_tiles_and_radii(shape, fwhm):
     # Tiles of 64 positions and 32 channels, segments shorter and longer than
-    # the halo, the widest fused radius (12) and the first beyond it. The in-place
-    # call takes the two passes, which sum the same taps in the same order.
+    # the halo, the widest fused radius (12), fused on a wide map and in two
+    # passes on a small one, and the first beyond it. The in-place call takes the two passes, which sum the same taps in the same order.
     say(f"[beam] shape={shape} fwhm={fwhm}")
     a = _rand_cube(shape, 4)
     t = torch.from_numpy(a).cuda()
