@@ -35,10 +35,12 @@ CFLAGS = [
 ]
 
 
-# Per source: the march keeps more wavefronts resident without loop-invariant
-# code motion on machine code, which holds the constants of its rarely taken
-# branches in vector registers across the whole march (107 -> 76 registers).
-SOURCE_FLAGS = {"forward.hip": ["-mllvm", "-disable-machine-licm"]}
+# Per source: the marches keep more wavefronts resident without loop-invariant
+# code motion on machine code, which holds the constants of rarely taken
+# branches in vector registers across the whole march (formal march 107 -> 76
+# registers; smooth march of 800 channels 694 -> 578 us).
+_NO_LICM = ["-mllvm", "-disable-machine-licm"]
+SOURCE_FLAGS = {"forward.hip": _NO_LICM, "smooth.hip": _NO_LICM, "thin.hip": _NO_LICM}
 
 
 # Sources whose host code validates arguments, folds constants, carves

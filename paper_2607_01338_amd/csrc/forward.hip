@@ -14,8 +14,9 @@
 //  * Per-cell physics (LTE populations, optical depths, source functions,
 //    channel window of the line) is computed lane-parallel for W cells of
 //    each sightline at a time from coalesced loads (cell_setup.h). The
-//    results go to a small LDS table that the march reads back as uniform
-//    128-bit loads, one row per cell.
+//    results go to a small LDS table by field; the march reads a field of W
+//    cells at a time, one per lane, and takes the cell's value from its lane
+//    by a row broadcast in the instruction that uses it.
 //  * The continuum march and the dust optical-depth prefix P_n are
 //    channel-independent prefix sums over those lanes: FP32 inside a chunk
 //    (at most W terms, relative to the chunk's base), FP64 across chunks. A
