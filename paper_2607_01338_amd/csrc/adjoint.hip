@@ -52,6 +52,18 @@
 // quantities of a segment go to an LDS table per sightline, the window sums
 // are group reductions, and the FP64 recurrences run group-uniform in every
 // lane. Per-cell window sums are FP32; recurrences and gradients are FP64.
+//
+// Register march (kReg): with four sightlines per wavefront a sightline's 16
+// lanes are one DPP row, and a segment of 16 cells has one cell per lane. Where
+// every cell's window fits one pass and the base does not move (the usual
+// segment), the tables and the tape stay in registers: a cell's values reach
+// its row by row broadcasts inside the instructions that use them, the 16-cell
+// loops are unrolled, and the window sums of the 16 cells reduce together
+// (row_merge). The march is bound by vector issue at two wavefronts per SIMD
+// (which the LDS of the other segments' tables leaves, 19 KB per wavefront at
+// 256 channels): 256^3 cells x 256 channels, FP32, 1660 us by the tables (136
+// vector and 20 LDS instructions per cell and wavefront, two exponentials each
+// way), 960 us like this (87 and 7, two exponentials in all).
 
 #include "cell_partials.h"
 #include "cell_setup.h"
@@ -136,6 +148,57 @@ __device__ __forceinline__ GenRev gen_reverse(float x, float E, float kd, float 
   return g;
 }
 
+// Four floats at once: in LDS, and from any 4-byte address of global memory.
+typedef float v4f __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ v4f gload4(const float* p) {
+  typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
+  return *(const __attribute__((address_space(1))) v4f_any*)p;
+}
+
+// Cells of a segment that the register march takes (one per lane of a row).
+constexpr int kAdjReg = 16;
+
+template <int... I, typename F>
+__device__ __forceinline__ void for_each_int(std::integer_sequence<int, I...>, F&& f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+
+// Sums over a row of 16 lanes of two quantities at once: where lanes that
+// differ in bit B hold partial sums of a and b, the lanes with the bit clear
+// go on with a's pairs and the others with b's. Four levels (B = 8, 4, 2, 1)
+// reduce 16 quantities in 45 instructions where one at a time takes 64, and
+// leave each in the lane whose index is its own with the bits reversed.
+template <int B>
+__device__ __forceinline__ float row_merge(float a, float b) {
+  // Contracted with the product it adds, the lane move would not fold into the add.
+#pragma clang fp contract(off)
+  // row_ror:8, row_half_mirror, quad_perm [2,3,0,1] and [1,0,3,2].
+  constexpr int ctrl = B == 8 ? kDppRowRor + 8 : B == 4 ? 0x141 : B == 2 ? 0x4E : 0xB1;
+  constexpr uint64_t mask = B == 8   ? 0xFF00FF00FF00FF00ull
+                            : B == 4 ? 0xF0F0F0F0F0F0F0F0ull
+                            : B == 2 ? 0xCCCCCCCCCCCCCCCCull
+                                     : 0xAAAAAAAAAAAAAAAAull;
+  a += dpp_f32<ctrl, 0xF>(a);
+  b += dpp_f32<ctrl, 0xF>(b);
+  return __builtin_amdgcn_inverse_ballot_w64(mask) ? b : a;
+}
+// The value of lane 15 - i of the row of 16.
+__device__ __forceinline__ float row_mirror(float x) { return dpp_f32<0x140, 0xF>(x); }
+__device__ __forceinline__ double row_mirror(double x) { return dpp_f64<0x140, 0xF>(x); }
+__device__ __forceinline__ int row_mirror(int x) {
+  return __builtin_amdgcn_mov_dpp(x, 0x140, 0xF, 0xF, true);
+}
+
+// Window sums of a cell's reverse step.
+struct RevSums {
+  float s1, s3, s4, s5;
+};
+template <int B>
+__device__ __forceinline__ RevSums row_merge(const RevSums& a, const RevSums& b) {
+  return {row_merge<B>(a.s1, b.s1), row_merge<B>(a.s3, b.s3), row_merge<B>(a.s4, b.s4),
+          row_merge<B>(a.s5, b.s5)};
+}
+
 template <typename L>
 struct AdjLoaderMaker;
 template <typename FT>
@@ -151,6 +214,17 @@ struct AdjLoaderMaker<DynLoader> {
   }
 };
 
+// What a lane keeps of the cell it set up in the register march.
+struct RegCell {
+  // Profile and state row: the profile argument is A (lane + off), the depth
+  // zero without a window.
+  float G, A, off, lk, emlk;
+  int k4, np;                // byte offset of the window's first channel, passes (0 or 1)
+  float omen, epex, Bm;
+  double an;
+  float lnn, T, X;
+};
+
 // Reverse march of sightlines pix0 .. pix0+G-1 by one wavefront; `lw` is its
 // LDS (adj_wave_floats floats, four more per cell of a segment with separate
 // source functions).
@@ -158,6 +232,7 @@ template <typename LoaderT, int G, bool GEN>
 __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float* lw) {
   constexpr int W = 64 / G;
   constexpr int RW = GEN ? kAdjRowGen : kAdjRow;  // floats per row
+  constexpr bool kReg = G == 4 && !GEN;           // register march where it applies
   const int lane = threadIdx.x & 63;
   const int sub = lane / W, sl = lane % W;
   const int64_t pix = pix0 + sub;
@@ -259,20 +334,48 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
   constexpr int kPf = kAhead ? 512 / W : 1;
   const bool pf_ck = kAhead && C <= kPf * W;
   typename LoaderT::Raw pre_f;
-  float pre_ck[kPf];
+  // Channels 4 (sl + b W) .. + 3 below the last multiple of four, then one of
+  // the remainder.
+  v4f pre_ck[kPf / 4 + 1];
+  float pre_rem = 0.f;
+  const int C4 = C & ~3;
   auto fetch_segment = [&](int gg) {
     const int i = gg * K + sl;
     pre_f = load.fetch((int64_t)i * P.at.los, live && sl < min(K, P.n_los - gg * K));
     if (pf_ck) {
       const float* src = P.ck_state + ((int64_t)gg * P.n_pix + pixc) * C;
 #pragma unroll
-      for (int b = 0; b < kPf; ++b) {
-        const int k = sl + b * W;
-        pre_ck[b] = k < C ? gload(src + k) : 0.f;
+      for (int b = 0; b < kPf / 4; ++b) {
+        const int k = 4 * (sl + b * W);
+        if (k < C4) pre_ck[b] = gload4(src + k);
       }
+      if (C4 + sl < C) pre_rem = gload(src + C4 + sl);
     }
   };
   if (kAhead) fetch_segment(n_seg - 1);
+
+  // The checkpointed line excess of segment g into the channel state, eight
+  // loads in flight per lane before their LDS stores (a load-use wait per
+  // element would serialise the HBM latency C/W times).
+  auto load_state = [&](int g) {
+    const float* src = P.ck_state + ((int64_t)g * P.n_pix + pixc) * C;
+    wave_order();
+    constexpr int kB = 8;
+    for (int k0 = sl; k0 < C; k0 += kB * W) {
+      float v[kB];
+#pragma unroll
+      for (int b = 0; b < kB; ++b) {
+        const int k = k0 + b * W;
+        v[b] = k < C ? gload(src + k) : 0.f;
+      }
+#pragma unroll
+      for (int b = 0; b < kB; ++b) {
+        const int k = k0 + b * W;
+        if (k < C) psi[k] = v[b];
+      }
+    }
+    wave_order();
+  };
 
   for (int g = n_seg - 1; g >= 0; --g) {
     const int s0 = g * K;
@@ -285,10 +388,11 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
     if (pf_ck) {
       wave_order();
 #pragma unroll
-      for (int b = 0; b < kPf; ++b) {
-        const int k = sl + b * W;
-        if (k < C) psi[k] = pre_ck[b];
+      for (int b = 0; b < kPf / 4; ++b) {
+        const int k = 4 * (sl + b * W);
+        if (k < C4) *(v4f*)(psi + k) = pre_ck[b];
       }
+      if (C4 + sl < C) psi[C4 + sl] = pre_rem;
       wave_order();
     }
     const typename LoaderT::Raw cur_f = pre_f;
@@ -301,6 +405,11 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
     double bcar = 0.0;  // that cell's base
     float Jcar = 0.f;   // its dust source function
     bool rebased = false;  // some cell of the segment (any group) moves the base
+    // Register march (kReg): lane i of a row holds cell i's profile and state,
+    // then its window sums.
+    bool in_regs = false;
+    RegCell rc;
+    RevSums rsum = {0.f, 0.f, 0.f, 0.f};
     for (int r = 0; r * W < L; ++r) {
       const int i = r * W + sl;
       const bool valid = live && i < L;
@@ -339,8 +448,24 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
         group_scan_affine<W>(M, Cc, Sd);
         Gn = fma(M, Gcar, Cc);
       }
-      if (i < L) {
-        const int np = valid ? window_passes(o.nwin, W) : 0;
+      const int np = valid ? window_passes(o.nwin, W) : 0;
+      if (kReg && K == kAdjReg && !round_moves && !__any(np > 1)) {
+        in_regs = true;
+        rc.G = np ? (float)Gn : 0.f;
+        rc.A = np ? o.A : 0.f;
+        rc.off = np ? o.c0 / o.A : 0.f;
+        rc.lk = np ? o.lk : -256.f;
+        rc.emlk = ex2(-o.lk);
+        rc.k4 = np ? 4 * o.kstart : 0;
+        rc.np = np;
+        rc.omen = valid ? one_minus_exp_neg(o.kD) : 0.f;
+        rc.epex = epf;
+        rc.an = Gn * (double)emf;
+        rc.Bm = (float)(Bs * (double)emf);
+        rc.lnn = in.lnn;
+        rc.T = in.T;
+        rc.X = in.X;
+      } else if (i < L) {
         float* rw = rows + i * RW;
         rw[kArG] = (float)Gn;
         rw[kArA] = o.A;
@@ -371,310 +496,364 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
       Jcar = __shfl(o.JD, last, 64);
     }
 
-    // Every cell of the segment (in every group) within one pass: the pass
-    // loops then need no per-cell bound across groups.
-    bool one_pass = true;
-    for (int i = sl; i < L; i += W)
-      if ((__float_as_int(rows[i * RW + kArPacked]) >> 24) > 1) one_pass = false;
-    one_pass = !__any(!one_pass);
-    // The two-cell loops below assume a base that does not move.
-    const bool pair = one_pass && !rebased;
-
-    // lambda~ from the base of the segment above (its start, P_{s1-1}) to the
-    // base of this segment's last cell: times e^{-(P_{s1-1} - P_{s0-1} - base)}.
-    wave_order();
-    if (Pcar > bcar) {
-      // Eight channels per lane in flight (a read-use wait per channel would
-      // serialise the LDS latency C/W times).
-      const float fsc = (float)exp(bcar - Pcar);
-      constexpr int kB = 8;
-      for (int k0 = sl; k0 < C; k0 += kB * W) {
-        float v[kB];
-#pragma unroll
-        for (int b = 0; b < kB; ++b) v[b] = k0 + b * W < C ? lam[k0 + b * W] : 0.f;
-#pragma unroll
-        for (int b = 0; b < kB; ++b)
-          if (k0 + b * W < C) lam[k0 + b * W] = v[b] * fsc;
-      }
-    }
-    wave_order();
-
-    int u1 = L;
-    while (u1 > 0) {
-      // Sub-segment [u0, u1): the longest suffix whose window passes fit
-      // the tape in every group (one cell always fits).
-      int u0 = u1;
-      if (one_pass) {
-        u0 = max(0, u1 - TP);  // at most one pass per cell
-      } else {
-        int tot = 0;
-        while (u0 > 0) {
-          const int np = __float_as_int(rows[(u0 - 1) * RW + kArPacked]) >> 24;
-          if (groups_max<G>(tot + np > TP ? 1 : 0)) break;
-          tot += np;
-          --u0;
-        }
-        if (u0 == u1) u0 = u1 - 1;
-      }
-      // Recompute the forward from the checkpoint to u1, taping [u0, u1).
-      if (pf_ck && u1 == L) {
-        // Already in place from the prefetch.
-      } else {
-        // Eight loads in flight per lane before their LDS stores (a load-use
-        // wait per element would serialise the HBM latency C/W times).
-        const float* src = P.ck_state + ((int64_t)g * P.n_pix + pixc) * C;
+    if (in_regs) {
+      if constexpr (kReg) {
+        // One pass per cell and one base: the cells' rows stay in the lanes
+        // that set them up, the tape (Psi + G, tau_L and 1 - e^{-tau_L} of
+        // every window lane) in registers, so that a cell costs LDS one read
+        // and one write each way. A cell without a window has tau_L = 0, which
+        // leaves the state as it is. The channels from C on (no cotangent,
+        // lambda = 0) start from zero in every segment.
+        if (!pf_ck) load_state(g);
+        psi[C + sl] = 0.f;
         wave_order();
+        auto at = [&](float* base, int k4) { return (float*)((char*)(base + sl) + k4); };
+        float pg[kAdjReg], tl[kAdjReg], ab[kAdjReg];
+        auto t_of = [&](auto ic) {
+          constexpr int i = decltype(ic)::value;
+          return (slf + row_bcast<i>(rc.off)) * row_bcast<i>(rc.A);
+        };
+        for_each_int(std::make_integer_sequence<int, kAdjReg>{}, [&](auto ic) {
+          constexpr int i = decltype(ic)::value;
+          const float t = t_of(ic);
+          tl[i] = ex2(fmaf(-t, t, row_bcast<i>(rc.lk)));
+          ab[i] = line_absorbed(tl[i]);
+          float* pk = at(psi, row_bcast<i>(rc.k4));
+          const float ps = *pk;
+          pg[i] = ps + row_bcast<i>(rc.G);
+          *pk = fmaf(-pg[i], ab[i], ps);
+          wave_order();
+        });
+        // lambda~ to the base of this segment (as below), and Q at its end
+        // over every channel.
+        const float fsc = Pcar > 0.0 ? (float)exp(-Pcar) : 1.f;
+        double qs = 0.0;
+        // Four channels at a time; those from C on add nothing (lambda = 0).
+#pragma unroll 2
+        for (int k = 4 * sl; k < C; k += 4 * W) {
+          const v4f a = *(const v4f*)(lam + k) * fsc;
+          const v4f b = *(const v4f*)(psi + k);
+          *(v4f*)(lam + k) = a;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) qs = fma((double)a[j], (double)b[j], qs);
+        }
+        Qend = group_sum<W>(qs);
+        wave_order();
+        auto reverse = [&](auto ic) {
+          constexpr int i = decltype(ic)::value;
+          const float t = t_of(ic);
+          float* lk = at(lam, row_bcast<i>(rc.k4));
+          const float lt = *lk;
+          const float le = fmaf(-lt, ab[i], lt);
+          *lk = le;
+          wave_order();
+          RevSums r;  // all but the sign
+          r.s1 = lt * ab[i];
+          r.s3 = le * pg[i] * (tl[i] * row_bcast<i>(rc.emlk));
+          r.s4 = r.s3 * t;
+          r.s5 = r.s4 * t;
+          return r;
+        };
+        // Cells 15 .. 0, merged as soon as two (four, eight) are there.
+        RevSums m8[2], m4[2], m2[2];
+        for_each_int(std::make_integer_sequence<int, kAdjReg / 2>{}, [&](auto jc) {
+          constexpr int p = kAdjReg / 2 - 1 - decltype(jc)::value;  // cells 2p + 1, 2p
+          const RevSums odd = reverse(std::integral_constant<int, 2 * p + 1>{});
+          const RevSums even = reverse(std::integral_constant<int, 2 * p>{});
+          m8[p & 1] = row_merge<8>(even, odd);
+          if constexpr (p % 2 == 0) m4[(p >> 1) & 1] = row_merge<4>(m8[0], m8[1]);
+          if constexpr (p % 4 == 0) m2[(p >> 2) & 1] = row_merge<2>(m4[0], m4[1]);
+          if constexpr (p == 0) rsum = row_merge<1>(m2[0], m2[1]);
+        });
+      }
+    } else {
+      // Every cell of the segment (in every group) within one pass: the pass
+      // loops then need no per-cell bound across groups.
+      bool one_pass = true;
+      for (int i = sl; i < L; i += W)
+        if ((__float_as_int(rows[i * RW + kArPacked]) >> 24) > 1) one_pass = false;
+      one_pass = !__any(!one_pass);
+      // The two-cell loops below assume a base that does not move.
+      const bool pair = one_pass && !rebased;
+
+      // lambda~ from the base of the segment above (its start, P_{s1-1}) to the
+      // base of this segment's last cell: times e^{-(P_{s1-1} - P_{s0-1} - base)}.
+      wave_order();
+      if (Pcar > bcar) {
+        // Eight channels per lane in flight (a read-use wait per channel would
+        // serialise the LDS latency C/W times).
+        const float fsc = (float)exp(bcar - Pcar);
         constexpr int kB = 8;
         for (int k0 = sl; k0 < C; k0 += kB * W) {
           float v[kB];
 #pragma unroll
-          for (int b = 0; b < kB; ++b) {
-            const int k = k0 + b * W;
-            v[b] = k < C ? gload(src + k) : 0.f;
-          }
+          for (int b = 0; b < kB; ++b) v[b] = k0 + b * W < C ? lam[k0 + b * W] : 0.f;
 #pragma unroll
-          for (int b = 0; b < kB; ++b) {
-            const int k = k0 + b * W;
-            if (k < C) psi[k] = v[b];
-          }
-        }
-        wave_order();
-      }
-      int toff = 0;
-      int i0 = 0;
-      if (pair) {
-        // Two cells per iteration (at most one pass each): both rows and
-        // exponentials ahead of the two state updates, which may touch the
-        // same channels and stay in order.
-        for (; i0 + 1 < u1; i0 += 2) {
-          float x[2], g[2];
-          float4 rg[2];  // h, kD, e^{kD} (separate source functions)
-          int k[2], np[2];
-#pragma unroll
-          for (int u = 0; u < 2; ++u) {
-            const float* rw = rows + (i0 + u) * RW;
-            const float4 ra = *(const float4*)rw;
-            const int pk = __float_as_int(rw[kArPacked]);
-            np[u] = pk >> 24;
-            k[u] = (pk & 0xFFFFFF) + sl;
-            const float t = fmaf(slf, ra.y, ra.z);
-            x[u] = ex2(fmaf(-t, t, ra.w));  // tau_L log2 e
-            g[u] = ra.x;
-            if (GEN) rg[u] = *(const float4*)(rw + kArH);
-          }
-          wave_order();
-#pragma unroll
-          for (int u = 0; u < 2; ++u) {
-            const float ps = psi[k[u]];  // every lane: no branch around the read
-            if (np[u]) {
-              if (i0 + u >= u0) tape[toff + sl] = ps;
-              psi[k[u]] = GEN ? gen_formal_step(ps, g[u], x[u], rg[u].x, rg[u].y, rg[u].z)
-                              : formal_line_step(ps, g[u], x[u]);
-            }
-            if (i0 + u >= u0) toff += W * np[u];
-            wave_order();
-          }
+          for (int b = 0; b < kB; ++b)
+            if (k0 + b * W < C) lam[k0 + b * W] = v[b] * fsc;
         }
       }
-      for (int i = i0; i < u1; ++i) {
-        const float* rw = rows + i * RW;
-        const float4 ra = *(const float4*)rw;
-        const int pk = __float_as_int(rw[kArPacked]);
-        const int np = pk >> 24, kstart = pk & 0xFFFFFF;
-        if (rebased && rw[kArRs] != 1.f) {
-          // The cell's base lies above its predecessor's: rescale the state.
-          const float rs = rw[kArRs];
-          wave_order();
-          for (int k = sl; k < C; k += W) psi[k] *= rs;
-          wave_order();
+      wave_order();
+
+      int u1 = L;
+      while (u1 > 0) {
+        // Sub-segment [u0, u1): the longest suffix whose window passes fit
+        // the tape in every group (one cell always fits).
+        int u0 = u1;
+        if (one_pass) {
+          u0 = max(0, u1 - TP);  // at most one pass per cell
+        } else {
+          int tot = 0;
+          while (u0 > 0) {
+            const int np = __float_as_int(rows[(u0 - 1) * RW + kArPacked]) >> 24;
+            if (groups_max<G>(tot + np > TP ? 1 : 0)) break;
+            tot += np;
+            --u0;
+          }
+          if (u0 == u1) u0 = u1 - 1;
         }
-        const int npm = one_pass ? (__any(np > 0) ? 1 : 0) : groups_max<G>(np);
-        if (npm == 0) continue;
-        const bool rec = i >= u0;
-        const float4 rg = GEN ? *(const float4*)(rw + kArH) : make_float4(0.f, 0.f, 0.f, 0.f);
-        wave_order();
-        for (int q = 0; q < npm; ++q) {
-          if (q < np) {
-            const int k = kstart + W * q + sl;
-            const float t = fmaf(slf + (float)(W * q), ra.y, ra.z);
-            const float ps = psi[k];
-            if (rec) tape[toff + W * q + sl] = ps;
-            const float x = ex2(fmaf(-t, t, ra.w));
-            psi[k] = GEN ? gen_formal_step(ps, ra.x, x, rg.x, rg.y, rg.z)
-                         : formal_line_step(ps, ra.x, x);
-          }
+        // Recompute the forward from the checkpoint to u1, taping [u0, u1).
+        if (pf_ck && u1 == L) {
+          // Already in place from the prefetch.
+        } else {
+          load_state(g);
         }
-        if (rec) toff += W * np;
-        wave_order();
-      }
-      if (u1 == L) {
-        // Q at the segment end over every channel.
-        double qs = 0.0;
-        wave_order();
-        constexpr int kB = 8;
-        for (int k0 = sl; k0 < C; k0 += kB * W) {
-          float a[kB], b[kB];
-#pragma unroll
-          for (int j = 0; j < kB; ++j) {
-            const bool in = k0 + j * W < C;
-            a[j] = in ? lam[k0 + j * W] : 0.f;
-            b[j] = in ? psi[k0 + j * W] : 0.f;
-          }
-#pragma unroll
-          for (int j = 0; j < kB; ++j) qs = fma((double)a[j], (double)b[j], qs);
-        }
-        Qend = group_sum<W>(qs);
-      }
-      // Reverse over the sub-segment.
-      int i1 = u1 - 1;
-      if (pair) {
-        // Two cells per iteration (cells i, i-1): rows, exponentials and tape
-        // reads ahead of the two lambda updates, which stay in order.
-        for (; i1 - 1 >= u0; i1 -= 2) {
-          float E[2], tl[2], t[2], g[2], em[2], ps0[2];
-          float4 rg[2];  // h, kD, e^{kD} (separate source functions)
-          int k[2], np[2];
-#pragma unroll
-          for (int u = 0; u < 2; ++u) {
-            const float* rw = rows + (i1 - u) * RW;
-            const float4 ra = *(const float4*)rw;
-            const float4 rb = *(const float4*)(rw + 4);
-            if (GEN) rg[u] = *(const float4*)(rw + kArH);
-            const int pk = __float_as_int(rb.y);
-            np[u] = pk >> 24;
-            k[u] = (pk & 0xFFFFFF) + sl;
-            t[u] = fmaf(slf, ra.y, ra.z);
-            tl[u] = ex2(fmaf(-t[u], t[u], ra.w));
-            E[u] = ex2(-tl[u]);
-            g[u] = ra.x;
-            em[u] = rb.x;
-            toff -= W * np[u];
-            // Read by every lane (a cell without passes reads LDS it ignores),
-            // so that no branch holds the two cells' reads apart.
-            const float tv = tape[toff + sl];
-            ps0[u] = np[u] ? tv : 0.f;
-          }
-          wave_order();
-          // The lambda updates stay in order; the window sums come after both,
-          // as selects, off the chain.
-          float s1[2], s3[2], s4[2], s5[2], sh[2], sk[2], lt[2];
-#pragma unroll
-          for (int u = 0; u < 2; ++u) {
-            lt[u] = lam[k[u]];
-            if (np[u]) lam[k[u]] = lt[u] * E[u];
-            wave_order();
-          }
-#pragma unroll
-          for (int u = 0; u < 2; ++u) {
-            const bool on = np[u] != 0 && k[u] < C;
-            float tg;  // taubar * g
-            if (GEN) {
-              const GenRev gr = gen_reverse(tl[u], E[u], rg[u].y, rg[u].z);
-              tg = lt[u] * fmaf(rg[u].x, gr.tb, -E[u] * (ps0[u] + g[u])) * (tl[u] * em[u]);
-              sh[u] = on ? lt[u] * gr.sh : 0.f;
-              sk[u] = on ? lt[u] * gr.sk : 0.f;
-            } else {
-              tg = -E[u] * lt[u] * (ps0[u] + g[u]) * (tl[u] * em[u]);
-            }
-            s1[u] = on ? lt[u] * (E[u] - 1.f) : 0.f;
-            s3[u] = on ? tg : 0.f;
-            s4[u] = on ? tg * t[u] : 0.f;
-            s5[u] = on ? tg * t[u] * t[u] : 0.f;
-          }
-#pragma unroll
-          for (int u = 0; u < 2; ++u) {
-            s1[u] = group_allsum<W>(s1[u]);
-            s3[u] = group_allsum<W>(s3[u]);
-            s4[u] = group_allsum<W>(s4[u]);
-            s5[u] = group_allsum<W>(s5[u]);
-            if (GEN) {
-              sh[u] = group_allsum<W>(sh[u]);
-              sk[u] = group_allsum<W>(sk[u]);
-            }
-          }
-          if (sl == 0) {
+        int toff = 0;
+        int i0 = 0;
+        if (pair) {
+          // Two cells per iteration (at most one pass each): both rows and
+          // exponentials ahead of the two state updates, which may touch the
+          // same channels and stay in order.
+          for (; i0 + 1 < u1; i0 += 2) {
+            float x[2], g[2];
+            float4 rg[2];  // h, kD, e^{kD} (separate source functions)
+            int k[2], np[2];
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-              float* rr = res + (i1 - u) * kAdjRes;
-              rr[kAsS1] = s1[u];
-              rr[kAsS3] = s3[u];
-              rr[kAsS4] = s4[u];
-              rr[kAsS5] = s5[u];
-              if (GEN) {
-                rr[kAsSH] = sh[u];
-                rr[kAsSK] = sk[u];
+              const float* rw = rows + (i0 + u) * RW;
+              const float4 ra = *(const float4*)rw;
+              const int pk = __float_as_int(rw[kArPacked]);
+              np[u] = pk >> 24;
+              k[u] = (pk & 0xFFFFFF) + sl;
+              const float t = fmaf(slf, ra.y, ra.z);
+              x[u] = ex2(fmaf(-t, t, ra.w));  // tau_L log2 e
+              g[u] = ra.x;
+              if (GEN) rg[u] = *(const float4*)(rw + kArH);
+            }
+            wave_order();
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+              const float ps = psi[k[u]];  // every lane: no branch around the read
+              if (np[u]) {
+                if (i0 + u >= u0) tape[toff + sl] = ps;
+                psi[k[u]] = GEN ? gen_formal_step(ps, g[u], x[u], rg[u].x, rg[u].y, rg[u].z)
+                                : formal_line_step(ps, g[u], x[u]);
               }
+              if (i0 + u >= u0) toff += W * np[u];
+              wave_order();
             }
           }
         }
-      }
-      for (int i = i1; i >= u0; --i) {
-        const float* rw = rows + i * RW;
-        const float4 ra = *(const float4*)rw;
-        const float4 rb = *(const float4*)(rw + 4);
-        const int pk = __float_as_int(rb.y);
-        const int np = pk >> 24, kstart = pk & 0xFFFFFF;
-        const int npm = one_pass ? (__any(np > 0) ? 1 : 0) : groups_max<G>(np);
-        float s1 = 0.f, s3 = 0.f, s4 = 0.f, s5 = 0.f, sh = 0.f, sk = 0.f;
-        if (npm > 0) {
+        for (int i = i0; i < u1; ++i) {
+          const float* rw = rows + i * RW;
+          const float4 ra = *(const float4*)rw;
+          const int pk = __float_as_int(rw[kArPacked]);
+          const int np = pk >> 24, kstart = pk & 0xFFFFFF;
+          if (rebased && rw[kArRs] != 1.f) {
+            // The cell's base lies above its predecessor's: rescale the state.
+            const float rs = rw[kArRs];
+            wave_order();
+            for (int k = sl; k < C; k += W) psi[k] *= rs;
+            wave_order();
+          }
+          const int npm = one_pass ? (__any(np > 0) ? 1 : 0) : groups_max<G>(np);
+          if (npm == 0) continue;
+          const bool rec = i >= u0;
           const float4 rg = GEN ? *(const float4*)(rw + kArH) : make_float4(0.f, 0.f, 0.f, 0.f);
-          toff -= W * np;
           wave_order();
           for (int q = 0; q < npm; ++q) {
             if (q < np) {
               const int k = kstart + W * q + sl;
               const float t = fmaf(slf + (float)(W * q), ra.y, ra.z);
-              const float tl = ex2(fmaf(-t, t, ra.w));
-              const float E = ex2(-tl);
-              const float lt = lam[k];
-              const float ps0 = tape[toff + W * q + sl];
-              if (k < C) {
-                s1 = fmaf(lt, E - 1.f, s1);
-                float tb = -E * lt * (ps0 + ra.x);
-                if (GEN) {
-                  const GenRev gr = gen_reverse(tl, E, rg.y, rg.z);
-                  tb = lt * fmaf(rg.x, gr.tb, -E * (ps0 + ra.x));
-                  sh = fmaf(lt, gr.sh, sh);
-                  sk = fmaf(lt, gr.sk, sk);
-                }
-                const float tg = tb * (tl * rb.x);  // taubar * g
-                s3 += tg;
-                s4 = fmaf(tg, t, s4);
-                s5 = fmaf(tg * t, t, s5);
-              }
-              lam[k] = lt * E;
+              const float ps = psi[k];
+              if (rec) tape[toff + W * q + sl] = ps;
+              const float x = ex2(fmaf(-t, t, ra.w));
+              psi[k] = GEN ? gen_formal_step(ps, ra.x, x, rg.x, rg.y, rg.z)
+                           : formal_line_step(ps, ra.x, x);
             }
           }
+          if (rec) toff += W * np;
           wave_order();
-          s1 = group_allsum<W>(s1);
-          s3 = group_allsum<W>(s3);
-          s4 = group_allsum<W>(s4);
-          s5 = group_allsum<W>(s5);
-          if (GEN) {
-            sh = group_allsum<W>(sh);
-            sk = group_allsum<W>(sk);
+        }
+        if (u1 == L) {
+          // Q at the segment end over every channel.
+          double qs = 0.0;
+          wave_order();
+          constexpr int kB = 8;
+          for (int k0 = sl; k0 < C; k0 += kB * W) {
+            float a[kB], b[kB];
+#pragma unroll
+            for (int j = 0; j < kB; ++j) {
+              const bool in = k0 + j * W < C;
+              a[j] = in ? lam[k0 + j * W] : 0.f;
+              b[j] = in ? psi[k0 + j * W] : 0.f;
+            }
+#pragma unroll
+            for (int j = 0; j < kB; ++j) qs = fma((double)a[j], (double)b[j], qs);
+          }
+          Qend = group_sum<W>(qs);
+        }
+        // Reverse over the sub-segment.
+        int i1 = u1 - 1;
+        if (pair) {
+          // Two cells per iteration (cells i, i-1): rows, exponentials and tape
+          // reads ahead of the two lambda updates, which stay in order.
+          for (; i1 - 1 >= u0; i1 -= 2) {
+            float E[2], tl[2], t[2], g[2], em[2], ps0[2];
+            float4 rg[2];  // h, kD, e^{kD} (separate source functions)
+            int k[2], np[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+              const float* rw = rows + (i1 - u) * RW;
+              const float4 ra = *(const float4*)rw;
+              const float4 rb = *(const float4*)(rw + 4);
+              if (GEN) rg[u] = *(const float4*)(rw + kArH);
+              const int pk = __float_as_int(rb.y);
+              np[u] = pk >> 24;
+              k[u] = (pk & 0xFFFFFF) + sl;
+              t[u] = fmaf(slf, ra.y, ra.z);
+              tl[u] = ex2(fmaf(-t[u], t[u], ra.w));
+              E[u] = ex2(-tl[u]);
+              g[u] = ra.x;
+              em[u] = rb.x;
+              toff -= W * np[u];
+              // Read by every lane (a cell without passes reads LDS it ignores),
+              // so that no branch holds the two cells' reads apart.
+              const float tv = tape[toff + sl];
+              ps0[u] = np[u] ? tv : 0.f;
+            }
+            wave_order();
+            // The lambda updates stay in order; the window sums come after both,
+            // as selects, off the chain.
+            float s1[2], s3[2], s4[2], s5[2], sh[2], sk[2], lt[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+              lt[u] = lam[k[u]];
+              if (np[u]) lam[k[u]] = lt[u] * E[u];
+              wave_order();
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+              const bool on = np[u] != 0 && k[u] < C;
+              float tg;  // taubar * g
+              if (GEN) {
+                const GenRev gr = gen_reverse(tl[u], E[u], rg[u].y, rg[u].z);
+                tg = lt[u] * fmaf(rg[u].x, gr.tb, -E[u] * (ps0[u] + g[u])) * (tl[u] * em[u]);
+                sh[u] = on ? lt[u] * gr.sh : 0.f;
+                sk[u] = on ? lt[u] * gr.sk : 0.f;
+              } else {
+                tg = -E[u] * lt[u] * (ps0[u] + g[u]) * (tl[u] * em[u]);
+              }
+              s1[u] = on ? lt[u] * (E[u] - 1.f) : 0.f;
+              s3[u] = on ? tg : 0.f;
+              s4[u] = on ? tg * t[u] : 0.f;
+              s5[u] = on ? tg * t[u] * t[u] : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+              s1[u] = group_allsum<W>(s1[u]);
+              s3[u] = group_allsum<W>(s3[u]);
+              s4[u] = group_allsum<W>(s4[u]);
+              s5[u] = group_allsum<W>(s5[u]);
+              if (GEN) {
+                sh[u] = group_allsum<W>(sh[u]);
+                sk[u] = group_allsum<W>(sk[u]);
+              }
+            }
+            if (sl == 0) {
+#pragma unroll
+              for (int u = 0; u < 2; ++u) {
+                float* rr = res + (i1 - u) * kAdjRes;
+                rr[kAsS1] = s1[u];
+                rr[kAsS3] = s3[u];
+                rr[kAsS4] = s4[u];
+                rr[kAsS5] = s5[u];
+                if (GEN) {
+                  rr[kAsSH] = sh[u];
+                  rr[kAsSK] = sk[u];
+                }
+              }
+            }
           }
         }
-        if (sl == 0) {
-          float* rr = res + i * kAdjRes;
-          rr[kAsS1] = s1;
-          rr[kAsS3] = s3;
-          rr[kAsS4] = s4;
-          rr[kAsS5] = s5;
-          if (GEN) {
-            rr[kAsSH] = sh;
-            rr[kAsSK] = sk;
+        for (int i = i1; i >= u0; --i) {
+          const float* rw = rows + i * RW;
+          const float4 ra = *(const float4*)rw;
+          const float4 rb = *(const float4*)(rw + 4);
+          const int pk = __float_as_int(rb.y);
+          const int np = pk >> 24, kstart = pk & 0xFFFFFF;
+          const int npm = one_pass ? (__any(np > 0) ? 1 : 0) : groups_max<G>(np);
+          float s1 = 0.f, s3 = 0.f, s4 = 0.f, s5 = 0.f, sh = 0.f, sk = 0.f;
+          if (npm > 0) {
+            const float4 rg = GEN ? *(const float4*)(rw + kArH) : make_float4(0.f, 0.f, 0.f, 0.f);
+            toff -= W * np;
+            wave_order();
+            for (int q = 0; q < npm; ++q) {
+              if (q < np) {
+                const int k = kstart + W * q + sl;
+                const float t = fmaf(slf + (float)(W * q), ra.y, ra.z);
+                const float tl = ex2(fmaf(-t, t, ra.w));
+                const float E = ex2(-tl);
+                const float lt = lam[k];
+                const float ps0 = tape[toff + W * q + sl];
+                if (k < C) {
+                  s1 = fmaf(lt, E - 1.f, s1);
+                  float tb = -E * lt * (ps0 + ra.x);
+                  if (GEN) {
+                    const GenRev gr = gen_reverse(tl, E, rg.y, rg.z);
+                    tb = lt * fmaf(rg.x, gr.tb, -E * (ps0 + ra.x));
+                    sh = fmaf(lt, gr.sh, sh);
+                    sk = fmaf(lt, gr.sk, sk);
+                  }
+                  const float tg = tb * (tl * rb.x);  // taubar * g
+                  s3 += tg;
+                  s4 = fmaf(tg, t, s4);
+                  s5 = fmaf(tg * t, t, s5);
+                }
+                lam[k] = lt * E;
+              }
+            }
+            wave_order();
+            s1 = group_allsum<W>(s1);
+            s3 = group_allsum<W>(s3);
+            s4 = group_allsum<W>(s4);
+            s5 = group_allsum<W>(s5);
+            if (GEN) {
+              sh = group_allsum<W>(sh);
+              sk = group_allsum<W>(sk);
+            }
+          }
+          if (sl == 0) {
+            float* rr = res + i * kAdjRes;
+            rr[kAsS1] = s1;
+            rr[kAsS3] = s3;
+            rr[kAsS4] = s4;
+            rr[kAsS5] = s5;
+            if (GEN) {
+              rr[kAsSH] = sh;
+              rr[kAsSK] = sk;
+            }
+          }
+          if (rebased && rw[kArRs] != 1.f) {
+            // lambda~ down to the predecessor's base.
+            const float rs = rw[kArRs];
+            wave_order();
+            for (int k = sl; k < C; k += W) lam[k] *= rs;
+            wave_order();
           }
         }
-        if (rebased && rw[kArRs] != 1.f) {
-          // lambda~ down to the predecessor's base.
-          const float rs = rw[kArRs];
-          wave_order();
-          for (int k = sl; k < C; k += W) lam[k] *= rs;
-          wave_order();
-        }
+        u1 = u0;
       }
-      u1 = u0;
     }
 
     // Recurrences of the reverse march, then the chain rule to the stored
@@ -689,12 +868,39 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
       const int i = r * W + (W - 1 - sl);
       const bool vc = i < L;
       double M = 1.0, Cm = 0.0, S = 0.0, abar = 0.0, omen = 0.0, an = 0.0, Bm = 0.0;
-      if (vc) {
+      RevSums ws = {0.f, 0.f, 0.f, 0.f};
+      float lnn_i = 0.f, T_i = 0.f, X_i = 0.f;
+      if (in_regs) {
+        if constexpr (kReg) {
+          // Cell 15 - sl: its sums from the lane with the reversed index.
+          const int src = (lane & ~15) | (int)(15u ^ (__builtin_bitreverse32((uint32_t)sl) >> 28));
+          // Every lane takes part in the moves; a cell without a window sums
+          // to zero whatever the channels at offset 0 hold.
+          const float s1 = __shfl(rsum.s1, src, 64), s3 = __shfl(rsum.s3, src, 64);
+          const float s4 = __shfl(rsum.s4, src, 64), s5 = __shfl(rsum.s5, src, 64);
+          if (row_mirror(rc.np) != 0) ws = {-s1, -s3, -s4, -s5};
+          omen = (double)row_mirror(rc.omen);
+          an = row_mirror(rc.an);
+          Bm = (double)row_mirror(rc.Bm);
+          lnn_i = row_mirror(rc.lnn);
+          T_i = row_mirror(rc.T);
+          X_i = row_mirror(rc.X);
+          abar = (double)row_mirror(rc.epex) * (double)ws.s1;
+          M = 1.0 - omen;
+          Cm = abar;
+          S = an * abar;
+        }
+      } else if (vc) {
         const float* rw = rows + i * RW;
+        const float* rr = res + i * kAdjRes;
+        ws = {rr[kAsS1], rr[kAsS3], rr[kAsS4], rr[kAsS5]};
+        lnn_i = rr[kAsLnn];
+        T_i = rr[kAsT];
+        X_i = rr[kAsX];
         omen = (double)rw[kArOmen];
         an = *(const double*)(rw + kArAn);
         Bm = (double)rw[kArBm];
-        abar = (double)rw[kArEPex] * (double)res[i * kAdjRes + kAsS1];
+        abar = (double)rw[kArEPex] * (double)ws.s1;
         M = 1.0 - omen;
         Cm = abar;
         S = an * abar;
@@ -725,19 +931,18 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
           kDbar_i = fma((double)rw[kArH], (double)rr[kAsSK], kDbar_i);
         }
         const int s = s0 + i;
-        const double kLbar = (double)rr[kAsS3];
-        const CellPartials cp =
-            GEN && c.ot
-                ? cell_partials_ot(c, (double)rr[kAsLnn], (double)rr[kAsT], (double)rr[kAsX])
-                : cell_partials<GEN>(c, (double)rr[kAsLnn], (double)rr[kAsT], (double)rr[kAsX]);
+        const double kLbar = (double)ws.s3;
+        const CellPartials cp = GEN && c.ot
+                                    ? cell_partials_ot(c, (double)lnn_i, (double)T_i, (double)X_i)
+                                    : cell_partials<GEN>(c, (double)lnn_i, (double)T_i, (double)X_i);
         if (GEN && !cp.line_src) {
           // No line in the level grid's populations: J_L is J_D itself.
           Jbar += Hbar;
           Hbar = 0.0;
         }
         const double fac = 2.0 * cp.kL / cp.b;
-        const double vbar = fac * (double)rr[kAsS4] * (1.0 / (double)kSqrtLog2e);
-        const double bbar = fac * (double)rr[kAsS5] * (1.0 / (double)kLog2e);
+        const double vbar = fac * (double)ws.s4 * (1.0 / (double)kSqrtLog2e);
+        const double bbar = fac * (double)ws.s5 * (1.0 / (double)kLog2e);
         const double kDbar = cp.kD_clamped ? 0.0 : kDbar_i;
         double glnn = kLbar * cp.kL + kDbar * cp.kD - bsum * Bout * cp.kD_free;
         if (GEN) glnn += kLbar * cp.dkL_dlnn + Hbar * cp.dJL_dlnn;  // level grid's n_H2 slopes
@@ -767,7 +972,7 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
   }
 }
 
-// Register caps: four sightlines per wavefront need LDS for only two
+// Register caps: four sightlines per wavefront have LDS for only two
 // wavefronts per SIMD, so their kernels may use up to 256 VGPRs; narrower
 // packings keep three wavefronts per SIMD.
 template <typename FT, int G, bool GEN>

@@ -451,3 +451,21 @@ def test_gradients_in_the_type_of_the_fields(dt, transfer, layout, monkeypatch):
     for k, a in zip(names, got):
         assert a.dtype == dev[k].dtype
         assert torch.equal(a, ref[k].to(a.dtype)), k
+
+
+@pytest.mark.parametrize("n_los,n_chan,dt", [(1, 5, "f32"), (16, 64, "f64"), (37, 63, "f32"),
+                                             (48, 514, "bf16"), (33, 256, "f32")])
+def test_adjoint_register_march(n_los, n_chan, dt, monkeypatch):
+    # Segments of 16 cells whose windows fit one pass of 16 lanes: first and
+    # last segments of 1 to 16 cells, remainders of four channels, more channels
+    # than are loaded ahead, windows over both band edges and outside them,
+    # cells without the molecule, a group without a sightline. One cell at
+    # 4000 K needs two passes and sends its segment through LDS.
+    monkeypatch.setenv("IRIS_RT_ADJOINT_SIGHTLINES_PER_WAVE", "4")
+    cube = W.make_cube((3, 3, n_los), 2, W.Channels(n_chan, -0.25 * n_chan, 0.5), seed=97,
+                       v_rms_kms=0.2 * n_chan)
+    cube.x_tracer[:, 1, ::5] = 0.0
+    if n_los > 32:
+        cube.t_kin[0, 0, 20] = 4000.0
+    check_adjoint(cube, dt, 16, random_cot(cube.n_pix, n_chan, 12),
+                  line=line_dict(kappa_dust_cm2g=20.0), label="register march")
