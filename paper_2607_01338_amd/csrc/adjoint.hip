@@ -323,6 +323,7 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
   bsum = group_sum<W>(bsum) * (double)c.out_scale;
   const double Ptrue = gload(P.ck_scal + pixc * kCkScal + kCkPtrue);
   const double Bout = c.J_bg * exp(-Ptrue);
+  const int64_t gbase = P.gat.base(pixc);
   double Qend = 0.0;  // sum of lambda~ Psi over the channels at a segment's end
   const int n_seg = (P.n_los + K - 1) / K;
 
@@ -957,7 +958,7 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
           gT = fma(Jbar, cp.dJ_dT, gT);
         }
         const double gX = kLbar * cp.dkL_dX;
-        const int64_t off = P.gat.base(pix) + (int64_t)s * P.gat.los;
+        const int64_t off = gbase + (int64_t)s * P.gat.los;
         const double gr[5] = {glnn, gT, vbar, gX, gTd};
         store_grads<GEN>(P, off, has_td, gr);
       }
