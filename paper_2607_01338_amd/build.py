@@ -41,7 +41,7 @@ CFLAGS = [
 # registers; smooth march of 800 channels 694 -> 578 us).
 _NO_LICM = ["-mllvm", "-disable-machine-licm"]
 SOURCE_FLAGS = {"forward.hip": _NO_LICM, "smooth.hip": _NO_LICM, "thin.hip": _NO_LICM,
-                "adjoint.hip": _NO_LICM}
+                "adjoint.hip": _NO_LICM, "levels.hip": _NO_LICM}
 
 
 # Sources whose host code validates arguments, folds constants, carves

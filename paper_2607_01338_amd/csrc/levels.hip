@@ -4,8 +4,8 @@
 // Balance"; "Spectral-Line Configuration"; "Grid Precomputation").
 //
 // Host side: a reader of molecular data in the LAMDA .dat convention.
-// Device side: one wavefront per grid node (ln n_H2, chi, ln T) solves the
-// balance in FP64 by state reduction (Grassmann, Taksar and Heyman, "Regenerative
+// Device side: 16 lanes per grid node (ln n_H2, chi, ln T; a wavefront above 48
+// levels) solve the balance in FP64 by state reduction (Grassmann, Taksar and Heyman, "Regenerative
 // Analysis and Steady State Distributions for Markov Chains", 1985) on the rate
 // matrix held in registers. A node that cannot be reduced (a level with no
 // way down to the levels before it) is left to a second kernel, which replaces
@@ -82,17 +82,20 @@ struct LevelsParams {
 };
 
 // Interval and weight of T in partner p's tabulated temperatures, the end
-// values held beyond them.
+// values held beyond them. Called by whole wavefronts, a lane per temperature
+// (a search from the first would wait for memory at every step).
 __device__ __forceinline__ void coll_temp(const LevelsParams& P, int p, double T, int& k,
                                           double& w) {
   const double* tt = P.temps + P.temp_off[p];
   const int nt = P.n_temp[p];
   k = 0;
   w = 0.0;
-  if (T >= tt[nt - 1]) {
+  const int lane = threadIdx.x & 63;
+  const int below = __popcll(__ballot(lane < nt && tt[min(lane, nt - 1)] <= T));
+  if (below == nt) {
     k = nt - 1;
-  } else if (T > tt[0]) {
-    while (tt[k + 1] <= T) ++k;
+  } else if (below > 0) {
+    k = below - 1;
     w = (T - tt[k]) / (tt[k + 1] - tt[k]);
   }
 }
@@ -114,6 +117,53 @@ __device__ __forceinline__ void unroll_down(F&& f) {
 // Wavefronts of a reduction workgroup; they share one (chi, T).
 constexpr int kOtWaves = 4;
 
+// The off-diagonal rates i -> j at (T, chi) in LDS, NS doubles a row: radiative,
+// and collisional per n_H2. Rows and columns beyond L are zero. Called by every
+// thread of the workgroup.
+template <int NL, int NS = NL>
+__device__ __forceinline__ void ot_rates(const LevelsParams& P, double T, double chi, double* base,
+                                         double* coll) {
+  for (int i = threadIdx.x; i < NL * NS; i += blockDim.x) base[i] = coll[i] = 0.0;
+  __syncthreads();
+  for (int t = threadIdx.x; t < P.n_rad; t += blockDim.x) {
+    const int u = P.rad_u[t], l = P.rad_l[t];
+    const double A = P.rad_a[t], nb = P.rad_nbar[t];
+    atomicAdd(&base[u * NS + l], A * (1.0 + nb));
+    atomicAdd(&base[l * NS + u], P.g[u] / P.g[l] * A * nb);
+  }
+  // Listed collision rates, partner by partner (a partner lists each pair once,
+  // or once each way round); then each way's reverse by detailed balance, one
+  // exponential for all partners.
+  for (int p = 0; p < P.n_part; ++p) {
+    const double share = P.dens_a[p] + P.dens_b[p] / chi;
+    int k;
+    double w;
+    coll_temp(P, p, T, k, w);
+    const int* cu = P.coll_u + P.coll_off[p];
+    const int* cl = P.coll_l + P.coll_off[p];
+    const double* rates = P.rates + P.rate_off[p];
+#pragma unroll 4
+    for (int c = threadIdx.x; c < P.n_coll[p]; c += blockDim.x) {
+      const int u = gload(cu + c), l = gload(cl + c);
+      const double* r = rates + (long)k * P.n_coll[p] + c;
+      const double r0 = gload(r);
+      const double kul = w == 0.0 ? r0 : r0 + w * (gload(r + P.n_coll[p]) - r0);
+      coll[u * NS + l] += kul * share;  // a partner's pairs are all different
+    }
+    __syncthreads();
+  }
+  __syncthreads();  // also where there are no partners
+  for (int t = threadIdx.x; t < P.L * P.L; t += blockDim.x) {
+    const int i = t / P.L, j = t % P.L;
+    if (j >= i) continue;
+    const double d = coll[i * NS + j], u = coll[j * NS + i];
+    const double de = (P.E[i] - P.E[j]) / T, gg = P.g[i] / P.g[j];
+    if (d != 0.0) coll[j * NS + i] += d * gg * exp(-de);
+    if (u != 0.0) coll[i * NS + j] += u / gg * exp(de);
+  }
+  __syncthreads();
+}
+
 // State reduction of the level balance. The stationary populations of a chain
 // with rates q[i][j] (i -> j) need only its off-diagonal rates: eliminating
 // the last state n adds q[i][n] q[n][j] / s_n, s_n = sum_{j<n} q[n][j], to
@@ -129,12 +179,11 @@ constexpr int kOtWaves = 4;
 // q = base + n_H2 coll in LDS once for all of its nodes. 128 x 64 x 64 nodes
 // of 41 levels: 67.5 ms as one LDS elimination with pivoting per node (32 KB
 // of LDS a wavefront, every rate and its detailed-balance exponential per
-// node), 4.4 ms like this.
+// node), 4.4 ms like this. Since ot_reduce_rows_kernel, for more than kOtRows
+// levels.
 template <int NL>
 __global__ __launch_bounds__(64 * kOtWaves)
 __attribute__((amdgpu_waves_per_eu(NL <= 48 ? 4 : 3))) void ot_reduce_kernel(const LevelsParams P) {
-  // Rates i -> j, rows and columns beyond L zero: radiative, and collisional
-  // per n_H2.
   __shared__ double base[NL * NL], coll[NL * NL];
   const int L = P.L;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -142,32 +191,7 @@ __attribute__((amdgpu_waves_per_eu(NL <= 48 ? 4 : 3))) void ot_reduce_kernel(con
   const int i_t = pair % P.n_t, i_c = pair / P.n_t;
   const double chi = P.chi0 + i_c * P.dchi;
   const double T = exp(P.lnt0 + i_t * P.dlnt);
-  for (int i = threadIdx.x; i < NL * NL; i += blockDim.x) base[i] = coll[i] = 0.0;
-  __syncthreads();
-  for (int t = threadIdx.x; t < P.n_rad; t += blockDim.x) {
-    const int u = P.rad_u[t], l = P.rad_l[t];
-    const double A = P.rad_a[t], nb = P.rad_nbar[t];
-    atomicAdd(&base[u * NL + l], A * (1.0 + nb));
-    atomicAdd(&base[l * NL + u], P.g[u] / P.g[l] * A * nb);
-  }
-  // Collisions, partner by partner (a partner lists each pair once, or once
-  // each way round).
-  for (int p = 0; p < P.n_part; ++p) {
-    const double share = P.dens_a[p] + P.dens_b[p] / chi;
-    int k;
-    double w;
-    coll_temp(P, p, T, k, w);
-    for (int c = threadIdx.x; c < P.n_coll[p]; c += blockDim.x) {
-      const int u = P.coll_u[P.coll_off[p] + c], l = P.coll_l[P.coll_off[p] + c];
-      const double* r = P.rates + P.rate_off[p] + (long)c * P.n_temp[p];
-      const double kul = w == 0.0 ? r[k] : r[k] + w * (r[k + 1] - r[k]);
-      const double down = kul * share;
-      atomicAdd(&coll[u * NL + l], down);
-      atomicAdd(&coll[l * NL + u], down * (P.g[u] / P.g[l]) * exp(-(P.E[u] - P.E[l]) / T));
-    }
-    __syncthreads();
-  }
-  __syncthreads();  // also where there are no partners
+  ot_rates<NL>(P, T, chi, base, coll);
 
   const int n_lo = (int)((long)P.n_n * split / P.splits);
   const int n_hi = (int)((long)P.n_n * (split + 1) / P.splits);
@@ -225,6 +249,180 @@ __attribute__((amdgpu_waves_per_eu(NL <= 48 ? 4 : 3))) void ot_reduce_kernel(con
   }
 }
 
+// Lane N of each row of 16 lanes, in the whole row.
+template <int N>
+__device__ __forceinline__ double row_bcast64(double x) {
+  return __builtin_amdgcn_update_dpp(x, x, kDppRowNewBcast + N, 0xF, 0xF, true);
+}
+// x += (lane N of col, row by row) f, one instruction. (From a broadcast and a
+// multiply-add the compiler makes two.) A lane move reads a register at least
+// two instructions after a vector instruction wrote it, which nobody else checks
+// for inline assembly.
+template <int N>
+__device__ __forceinline__ void row_fmac64(double& x, const double& col, double f) {
+  asm("s_nop 1\n\tv_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+      : "+v"(x)
+      : "v"(col), "v"(f), "n"(N));
+}
+// The same where col itself is the sum: f is zero in lane N.
+template <int N>
+__device__ __forceinline__ void row_fmac64_self(double& col, double f) {
+  asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf"
+      : "+v"(col)
+      : "v"(f), "n"(N));
+}
+// Sum over each row of 16 lanes, in the whole row.
+__device__ __forceinline__ double row_allsum64(double x) {
+  x += dpp_f64<kDppRowRor + 8, 0xF>(x);
+  x += dpp_f64<kDppRowRor + 4, 0xF>(x);
+  x += dpp_f64<kDppRowRor + 2, 0xF>(x);
+  return x + dpp_f64<kDppRowRor + 1, 0xF>(x);
+}
+// 1 / x by two Newton steps on the hardware's estimate, to an ulp or two.
+__device__ __forceinline__ double recip64(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
+}
+
+// The same reduction, a density per row of 16 lanes: lane c of row r holds
+// columns c, c + 16, .. of the r-th of four neighbouring densities. Column n
+// reaches a node's lanes by a row broadcast inside the multiply-add, the pivot
+// row is already where it is used, and the row sums, the reciprocals and the
+// back substitution serve four nodes at once. Levels go in blocks of 16, the
+// last first: a block's columns are loaded when it is their turn and get what
+// the levels above add to them then, so that the matrix never lies in registers
+// as a whole (41 levels: 178 + 50 of them at most, two wavefronts per SIMD). A
+// step first updates the row that the next step sums, so that its chain (row
+// sum, reciprocal) runs beside the rest of the update. Bound by VALU issue.
+// 128 x 64 x 64 nodes of 41 levels: 4.4 ms a wavefront per node, 1.5 ms like
+// this (2.8 ms right-looking with the matrix in 288 registers, 1.8 ms with the
+// broadcasts as instructions of their own).
+template <int NL>
+__global__ __launch_bounds__(64 * kOtWaves)
+__attribute__((amdgpu_waves_per_eu(NL <= 24 ? 4 : NL <= 32 ? 3 : 2))) void ot_reduce_rows_kernel(
+    const LevelsParams P) {
+  constexpr int NB = (NL + 15) / 16;
+  constexpr int NS = 16 * NB;
+  __shared__ double base[NL * NS], coll[NL * NS];
+  const int L = P.L;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int pair = blockIdx.x / P.splits, split = blockIdx.x % P.splits;
+  const int i_t = pair % P.n_t, i_c = pair / P.n_t;
+  const double chi = P.chi0 + i_c * P.dchi;
+  const double T = exp(P.lnt0 + i_t * P.dlnt);
+  ot_rates<NL, NS>(P, T, chi, base, coll);
+
+  const int n_lo = (int)((long)P.n_n * split / P.splits);
+  const int n_hi = (int)((long)P.n_n * (split + 1) / P.splits);
+  for (int i0 = n_lo + 4 * wave; i0 < n_hi; i0 += 4 * kOtWaves) {
+    const int i_n = i0 + (lane >> 4);
+    const double nh2 = exp(P.lnn0 + min(i_n, n_hi - 1) * P.dlnn);
+    // Opaque, so that the lane masks of all steps are not kept in registers.
+    int c = lane & 15, nl = L;
+    asm volatile("" : "+v"(c), "+s"(nl));
+    double q[NL][NB];
+    auto load = [&](int i, int b) {
+      q[i][b] = fma(nh2, coll[i * NS + 16 * b + c], base[i * NS + 16 * b + c]);
+    };
+    double inv[NB];  // lane n: 1 / s_n
+    bool bad = false;
+    // Blocks of 16 levels, the last first.
+    unroll_down<NB>([&](auto block) {
+      constexpr int kb = decltype(block)::value - 1;
+      constexpr int lo = 16 * kb, hi = (lo + 16 < NL ? lo + 16 : NL) - 1;
+#pragma unroll
+      for (int i = 0; i <= hi; ++i) {
+#pragma unroll
+        for (int b = 0; b <= kb; ++b)
+          if (b == kb || i >= lo) load(i, b);
+        if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+      }
+      inv[kb] = 1.0;
+      // What the levels above the block add to it.
+      if constexpr (hi < NL - 1)
+        unroll_down<NL - 1 - hi>([&](auto step) {
+          constexpr int n = hi + decltype(step)::value;
+#pragma unroll
+          for (int i = 0; i <= hi; ++i) {
+#pragma unroll
+            for (int b = 0; b <= kb; ++b)
+              if (b == kb || i >= lo) row_fmac64<n % 16>(q[i][b], q[i][n / 16], q[n][b]);
+          }
+        });
+      // The pivot row of level n over s_n: in place below the block, whose own
+      // part goes to f (its row keeps the rates to the levels above n).
+      double f = 0.0;
+      auto pivot = [&](auto level) {
+        constexpr int n = decltype(level)::value;
+        f = c < n - lo ? q[n][kb] : 0.0;
+        double s = f;
+#pragma unroll
+        for (int b = 0; b < kb; ++b) s += q[n][b];
+        s = row_allsum64(s);
+        if (!(s > 0.0)) bad = true;
+        const double is = recip64(s);
+        if (c == n - lo) inv[kb] = is;
+        f *= is;
+#pragma unroll
+        for (int b = 0; b < kb; ++b) q[n][b] *= is;
+      };
+      unroll_down<hi - lo + 1>([&](auto step) {
+        constexpr int n = lo + decltype(step)::value - 1;
+        if constexpr (n > 0)
+          if (n < nl) {
+            if (n == hi || n == nl - 1) pivot(std::integral_constant<int, n>{});
+            const double g = f;
+            auto update = [&](int i) {
+              if (i >= lo) {
+#pragma unroll
+                for (int b = 0; b < kb; ++b) row_fmac64<n % 16>(q[i][b], q[i][kb], q[n][b]);
+              }
+              row_fmac64_self<n % 16>(q[i][kb], g);
+            };
+            // The next pivot row first: its sum and reciprocal are a chain.
+            if constexpr (n - 1 >= lo && n > 1) {
+              update(n - 1);
+              pivot(std::integral_constant<int, n - 1>{});
+            }
+#pragma unroll
+            for (int i = (n - 1 >= lo && n > 1 ? n - 2 : n - 1); i >= 0; --i) {
+              update(i);
+            }
+          }
+      });
+    });
+    // pi_n in every lane of the row: acc[b] collects sum_i pi_i q[i][c + 16 b].
+    int iu = P.u_obs, il = P.l_obs;
+    asm volatile("" : "+s"(iu), "+s"(il));
+    double acc[NB], p = 1.0, tot = 1.0;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b] = 0.0;
+    double pu = iu == 0 ? 1.0 : 0.0, pl = il == 0 ? 1.0 : 0.0;
+    unroll_down<NL - 1>([&](auto step) {
+      constexpr int n = NL - decltype(step)::value;
+      if (n < nl) {
+#pragma unroll
+        for (int b = n / 16; b < NB; ++b) acc[b] = fma(p, q[n - 1][b], acc[b]);
+        p = row_bcast64<n % 16>(acc[n / 16] * inv[n / 16]);
+        tot += p;
+        if (iu == n) pu = p;
+        if (il == n) pl = p;
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    });
+    if (!(tot < 1e300)) bad = true;  // also NaN
+    if (c == 0 && i_n < n_hi) {
+      const double fu = pu / tot, fl = pl / tot;
+      const double FU = P.g[P.l_obs] / P.g[P.u_obs] * fu;
+      const long pt = ((long)i_c * P.n_t + i_t) * P.n_n + i_n;
+      P.grid[pt] = bad ? make_float2(__builtin_nanf(""), 0.f)
+                       : make_float2((float)FU, (float)(fl - FU));
+      if (bad) atomicAdd(P.unreduced, 1);
+    }
+  }
+}
+
 // Pivoting elimination of the nodes that the state reduction left (their
 // stored FU is NaN), one wavefront each: lane j holds column j of the balance
 // in LDS, the right-hand side is column L.
@@ -257,14 +455,13 @@ __global__ __launch_bounds__(64) void ot_levels_kernel(const LevelsParams P) {
     // Collisions, partner by partner (a partner lists each pair once).
     for (int p = 0; p < P.n_part; ++p) {
       const double ns = nh2 * (P.dens_a[p] + P.dens_b[p] / chi);
-      const int nt = P.n_temp[p];
       int k;
       double w;
       coll_temp(P, p, T, k, w);
       for (int c = lane; c < P.n_coll[p]; c += 64) {
         const int u = P.coll_u[P.coll_off[p] + c], l = P.coll_l[P.coll_off[p] + c];
-        const double* r = P.rates + P.rate_off[p] + (long)c * nt;
-        const double kul = w == 0.0 ? r[k] : r[k] + w * (r[k + 1] - r[k]);
+        const double* r = P.rates + P.rate_off[p] + (long)k * P.n_coll[p] + c;
+        const double kul = w == 0.0 ? r[0] : r[0] + w * (r[P.n_coll[p]] - r[0]);
         const double down = kul * ns;
         M[l][u] += down;
         M[u][l] += down * (P.g[u] / P.g[l]) * exp(-(P.E[u] - P.E[l]) / T);
@@ -329,13 +526,20 @@ __global__ __launch_bounds__(64) void ot_levels_kernel(const LevelsParams P) {
   }
 }
 
-// The reduction compiled for the smallest multiple of 8 rows that holds L.
+// The reduction compiled for the smallest multiple of 8 rows (4 from 32 to 48)
+// that holds L. Up to kOtRows levels 16 lanes hold a node's part of the matrix
+// in the 256 registers of two wavefronts per SIMD; 63 levels would take 410.
+constexpr int kOtRows = 48;
 template <int NL>
 int launch_ot_reduce(const LevelsParams& P, int blocks, hipStream_t st) {
+  constexpr int kStep = NL > 32 && NL <= kOtRows ? 4 : 8;
   if constexpr (NL > 8)
-    if (P.L <= NL - 8) return launch_ot_reduce<NL - 8>(P, blocks, st);
-  hipLaunchKernelGGL((ot_reduce_kernel<(NL < kMaxLevels ? NL : kMaxLevels)>), dim3(blocks),
-                     dim3(64 * kOtWaves), 0, st, P);
+    if (P.L <= NL - kStep) return launch_ot_reduce<NL - kStep>(P, blocks, st);
+  if constexpr (NL <= kOtRows)
+    hipLaunchKernelGGL((ot_reduce_rows_kernel<NL>), dim3(blocks), dim3(64 * kOtWaves), 0, st, P);
+  else
+    hipLaunchKernelGGL((ot_reduce_kernel<(NL < kMaxLevels ? NL : kMaxLevels)>), dim3(blocks),
+                       dim3(64 * kOtWaves), 0, st, P);
   return (int)hipGetLastError();
 }
 
@@ -560,7 +764,9 @@ iris_status iris_levels_create(const iris_molecule* mol, const iris_levels_confi
     cu.insert(cu.end(), p.u.begin(), p.u.end());
     cl.insert(cl.end(), p.l.begin(), p.l.end());
     temps.insert(temps.end(), p.temps.begin(), p.temps.end());
-    rates.insert(rates.end(), p.rates.begin(), p.rates.end());
+    // By temperature: neighbouring lanes read neighbouring transitions.
+    for (size_t k = 0; k < p.temps.size(); ++k)
+      for (size_t c = 0; c < p.u.size(); ++c) rates.push_back(p.rates[c * p.temps.size() + k]);
   }
   P.n_part = (int)used.size();
   size_t off = 0;

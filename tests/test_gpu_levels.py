@@ -72,10 +72,12 @@ def test_grid_of_the_golden_three_level_molecule(transition, t_bar):
     lv.close()
 
 
-@pytest.mark.parametrize("n_levels", [2, 8, 9, 24, 25, 41, 48, 49, 63])
+@pytest.mark.parametrize("n_levels", [2, 8, 9, 16, 17, 24, 25, 32, 33, 36, 37, 41, 44, 48, 49,
+                                      63])
 def test_grid_at_the_edges_of_the_compiled_sizes(n_levels, tmp_path):
-    # The reduction is compiled for 8, 16, .., 56, 63 rows; densities that do
-    # not divide among a workgroup's wavefronts, one and several per workgroup.
+    # The reduction is compiled for 8, 16, .., 32, 36, .., 48 rows (columns in
+    # blocks of 16, four densities a wavefront) and for 56 and 63 (one density);
+    # densities that do not divide among a workgroup's wavefronts.
     path = str(tmp_path / "rotor.dat")
     W.write_lamda(path, W.synthetic_rotor_molecule(n_levels=n_levels, seed=n_levels))
     cfg = dict(n_n=5, n_chi=2, n_t=3, ln_nh2_lo=-2.0, ln_nh2_hi=16.0, chi_lo=0.3, chi_hi=1.0,
@@ -84,6 +86,19 @@ def test_grid_at_the_edges_of_the_compiled_sizes(n_levels, tmp_path):
     say(f"[levels] rotor of {n_levels} levels")
     lv = rt.Levels(rt.Molecule(path), transition, **cfg)
     assert_grid_close(lv.grid(), oracle_grid(Lv.read_lamda(path), cfg, transition), "rotor")
+    lv.close()
+
+
+def test_grid_with_several_rounds_of_densities(tmp_path):
+    # More (chi, T) pairs than the launch splits: 21 densities per workgroup,
+    # sixteen at a time, the last of the second round alone in its wavefront.
+    path = str(tmp_path / "rotor.dat")
+    W.write_lamda(path, W.synthetic_rotor_molecule(n_levels=5, seed=3))
+    cfg = dict(n_n=21, n_chi=33, n_t=125, ln_nh2_lo=-2.0, ln_nh2_hi=16.0, chi_lo=0.3, chi_hi=1.0,
+               t_lo_k=4.0, t_hi_k=900.0)
+    say("[levels] 21 x 33 x 125 grid of a rotor of 5 levels")
+    lv = rt.Levels(rt.Molecule(path), 2, **cfg)
+    assert_grid_close(lv.grid(), oracle_grid(Lv.read_lamda(path), cfg, 2), "rotor")
     lv.close()
 
 
