@@ -660,6 +660,7 @@ __global__ __launch_bounds__(256) void thin_adj_kernel(const AdjParams P, int sm
   wave_order();
   const DynLoader load(P.f, P.at.base(live ? pix : P.n_pix - 1), P.dtype);
   const bool has_td = GEN && P.f[4] != nullptr;
+  const int64_t gbase = P.gat.base(live ? pix : P.n_pix - 1);
   const float isl = 1.f / kSqrtLog2e;
 
   for (int s0 = 0; s0 < P.n_los; s0 += W) {
@@ -756,7 +757,7 @@ __global__ __launch_bounds__(256) void thin_adj_kernel(const AdjParams P, int sm
       double gTd = 0.0;
       if (has_td) gTd = bDe * kDn * planck_rj_dT(c, (double)in.Td);
       else gT += bDe * kDn * cp.dJ_dT;
-      const int64_t off = P.gat.base(pix) + (int64_t)s * P.gat.los;
+      const int64_t off = gbase + (int64_t)s * P.gat.los;
       const double gr[5] = {glnn, gT, gv, gX, gTd};
       store_grads<GEN>(P, off, has_td, gr);
     }
