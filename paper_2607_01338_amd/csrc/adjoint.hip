@@ -426,7 +426,7 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
       // of different lanes round differently.
       double bse = fmax(kAdjBaseStep * floor(Pex * (1.0 / kAdjBaseStep)), bcar);
       if (__any(bse > 0.0)) bse = group_scan_max<W>(bse);
-      const double bup = dpp_f64_keep<kDppWaveShr1, 0xF>(bse, 0.0);
+      const double bup = dpp_f64<kDppWaveShr1, 0xF>(bse);
       const double bprev = sl == 0 ? bcar : bup;
       const bool moved = valid && bse > bprev;
       const bool round_moves = __any(moved);
@@ -490,6 +490,11 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
         rr[kAsX] = in.X;
         if (GEN) rr[kAsTd] = in.Td;
       }
+      if (in_regs) {
+        // The only round: cells from L on have no dust and repeat the last prefix.
+        if constexpr (kReg) Pcar = row_bcast64<15>(Pin);
+        continue;
+      }
       const int last = sub * W + min(W, L - r * W) - 1;
       Pcar = __shfl(Pin, last, 64);
       Gcar = __shfl(Gn, last, 64);
@@ -538,7 +543,7 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
 #pragma unroll
           for (int j = 0; j < 4; ++j) qs = fma((double)a[j], (double)b[j], qs);
         }
-        Qend = group_sum<W>(qs);
+        Qend = row_allsum64(qs);
         wave_order();
         auto reverse = [&](auto ic) {
           constexpr int i = decltype(ic)::value;
@@ -911,8 +916,8 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
       group_scan_affine<W>(M, Cm, S);
       // Exclusive: the maps of the cells above this one (identity in lane 0).
       double Mx = dpp_f64_keep<kDppWaveShr1, 0xF>(M, 1.0);
-      double Cx = dpp_f64_keep<kDppWaveShr1, 0xF>(Cm, 0.0);
-      double Sx = dpp_f64_keep<kDppWaveShr1, 0xF>(S, 0.0);
+      double Cx = dpp_f64<kDppWaveShr1, 0xF>(Cm);
+      double Sx = dpp_f64<kDppWaveShr1, 0xF>(S);
       if (sl == 0) {
         Mx = 1.0;
         Cx = 0.0;
@@ -964,7 +969,16 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
       }
       // Carry the composition of the whole round (the group's last lane).
       const int last = sub * W + W - 1;
-      const double Ml = __shfl(M, last, 64), Cl = __shfl(Cm, last, 64), Sl = __shfl(S, last, 64);
+      double Ml, Cl, Sl;
+      if constexpr (W == 16) {
+        Ml = row_bcast64<15>(M);
+        Cl = row_bcast64<15>(Cm);
+        Sl = row_bcast64<15>(S);
+      } else {
+        Ml = __shfl(M, last, 64);
+        Cl = __shfl(Cm, last, 64);
+        Sl = __shfl(S, last, 64);
+      }
       gam = fma(Ml, gam, Cl);
       del = Ml * del;
       Qc -= Sl;

@@ -160,9 +160,15 @@ constexpr int kDppWaveShr1 = 0x138;
 constexpr int kDppRowNewBcast = 0x150;  // + n: lane n of each row of 16 to the whole row
 
 template <int Ctrl, int RowMask>
+__device__ __forceinline__ int dpp_i32(int x) {
+  // Over whole waves the move itself writes the zeros; with rows left out their
+  // register is cleared first.
+  if constexpr (RowMask == 0xF) return __builtin_amdgcn_mov_dpp(x, Ctrl, 0xF, 0xF, true);
+  return __builtin_amdgcn_update_dpp(0, x, Ctrl, RowMask, 0xF, false);
+}
+template <int Ctrl, int RowMask>
 __device__ __forceinline__ float dpp_f32(float x) {
-  return __int_as_float(
-      __builtin_amdgcn_update_dpp(0, __float_as_int(x), Ctrl, RowMask, 0xF, false));
+  return __int_as_float(dpp_i32<Ctrl, RowMask>(__float_as_int(x)));
 }
 
 // Lane N of each row of 16 lanes, in the whole row. The move folds into the
@@ -237,8 +243,8 @@ __device__ __forceinline__ int groups_max(int x) {
 template <int Ctrl, int RowMask>
 __device__ __forceinline__ double dpp_f64(double x) {
   const uint64_t u = (uint64_t)__double_as_longlong(x);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, Ctrl, RowMask, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), Ctrl, RowMask, 0xF, false);
+  const int lo = dpp_i32<Ctrl, RowMask>((int)(uint32_t)u);
+  const int hi = dpp_i32<Ctrl, RowMask>((int)(uint32_t)(u >> 32));
   return __longlong_as_double((long long)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
 }
 template <int W>
@@ -251,6 +257,19 @@ __device__ __forceinline__ double group_scan_dpp(double x) {
   if (W >= 32) x += dpp_f64<kDppRowBcast15, 0xA>(x);
   if (W == 64) x += dpp_f64<kDppRowBcast31, 0xC>(x);
   return x;
+}
+
+// Sum over each row of 16 lanes, FP64, in the whole row.
+__device__ __forceinline__ double row_allsum64(double x) {
+  x += dpp_f64<kDppRowRor + 8, 0xF>(x);
+  x += dpp_f64<kDppRowRor + 4, 0xF>(x);
+  x += dpp_f64<kDppRowRor + 2, 0xF>(x);
+  return x + dpp_f64<kDppRowRor + 1, 0xF>(x);
+}
+// Lane N of each row of 16 lanes, FP64, in the whole row.
+template <int N>
+__device__ __forceinline__ double row_bcast64(double x) {
+  return __builtin_amdgcn_update_dpp(x, x, kDppRowNewBcast + N, 0xF, 0xF, true);
 }
 
 // FP64 DPP move whose lanes without a source keep `old`.
@@ -274,8 +293,8 @@ __device__ __forceinline__ void group_scan_affine(double& M, double& C, double& 
   auto step = [&](auto ctrl_tag, auto mask_tag) {
     constexpr int kc = decltype(ctrl_tag)::value, km = decltype(mask_tag)::value;
     const double Mp = dpp_f64_keep<kc, km>(M, 1.0);
-    const double Cp = dpp_f64_keep<kc, km>(C, 0.0);
-    const double Sp = dpp_f64_keep<kc, km>(S, 0.0);
+    const double Cp = dpp_f64<kc, km>(C);
+    const double Sp = dpp_f64<kc, km>(S);
     C = fma(M, Cp, C);
     M = M * Mp;
     S = S + Sp;

@@ -249,11 +249,6 @@ __attribute__((amdgpu_waves_per_eu(NL <= 48 ? 4 : 3))) void ot_reduce_kernel(con
   }
 }
 
-// Lane N of each row of 16 lanes, in the whole row.
-template <int N>
-__device__ __forceinline__ double row_bcast64(double x) {
-  return __builtin_amdgcn_update_dpp(x, x, kDppRowNewBcast + N, 0xF, 0xF, true);
-}
 // x += (lane N of col, row by row) f, one instruction. (From a broadcast and a
 // multiply-add the compiler makes two.) A lane move reads a register at least
 // two instructions after a vector instruction wrote it, which nobody else checks
@@ -270,13 +265,6 @@ __device__ __forceinline__ void row_fmac64_self(double& col, double f) {
   asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf"
       : "+v"(col)
       : "v"(f), "n"(N));
-}
-// Sum over each row of 16 lanes, in the whole row.
-__device__ __forceinline__ double row_allsum64(double x) {
-  x += dpp_f64<kDppRowRor + 8, 0xF>(x);
-  x += dpp_f64<kDppRowRor + 4, 0xF>(x);
-  x += dpp_f64<kDppRowRor + 2, 0xF>(x);
-  return x + dpp_f64<kDppRowRor + 1, 0xF>(x);
 }
 // 1 / x by two Newton steps on the hardware's estimate, to an ulp or two.
 __device__ __forceinline__ double recip64(double x) {

@@ -26,14 +26,6 @@ struct TabNode {
 
 constexpr int kNodeLanes = 16;  // lanes of a node's partition sum (one DPP row)
 
-__device__ __forceinline__ double row_sum(double x) {
-  x += dpp_f64<kDppRowRor + 8, 0xF>(x);
-  x += dpp_f64<kDppRowRor + 4, 0xF>(x);
-  x += dpp_f64<kDppRowRor + 2, 0xF>(x);
-  x += dpp_f64<kDppRowRor + 1, 0xF>(x);
-  return x;
-}
-
 // The node at u by a row of 16 lanes (r = lane in the row): the terms of the
 // partition sum and the exponentials of the source functions are spread over
 // the lanes; every lane returns the node.
@@ -53,9 +45,9 @@ __device__ __forceinline__ TabNode tab_node(const TabParams& tp, double u, int r
     ZE += w * E;
     if (J == tp.j_l) el = e;
   }
-  Z = row_sum(Z);
-  ZE = row_sum(ZE);
-  el = row_sum(el);
+  Z = row_allsum64(Z);
+  ZE = row_allsum64(ZE);
+  el = row_allsum64(el);
   const double El = tp.theta * tp.j_l * (tp.j_l + 1.0);
   // e^{-dE/T} - 1, e^{T0/T} - 1 and e^{dE/T} - 1 in lanes 0, 1 and 2.
   const double x = tp.T0 * rT, y = tp.dE * rT;
