@@ -148,13 +148,6 @@ __device__ __forceinline__ GenRev gen_reverse(float x, float E, float kd, float 
   return g;
 }
 
-// Four floats at once: in LDS, and from any 4-byte address of global memory.
-typedef float v4f __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ v4f gload4(const float* p) {
-  typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
-  return *(const __attribute__((address_space(1))) v4f_any*)p;
-}
-
 // Cells of a segment that the register march takes (one per lane of a row).
 constexpr int kAdjReg = 16;
 
@@ -337,7 +330,7 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
   typename LoaderT::Raw pre_f;
   // Channels 4 (sl + b W) .. + 3 below the last multiple of four, then one of
   // the remainder.
-  v4f pre_ck[kPf / 4 + 1];
+  gv4f pre_ck[kPf / 4 + 1];
   float pre_rem = 0.f;
   const int C4 = C & ~3;
   auto fetch_segment = [&](int gg) {
@@ -391,7 +384,7 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
 #pragma unroll
       for (int b = 0; b < kPf / 4; ++b) {
         const int k = 4 * (sl + b * W);
-        if (k < C4) *(v4f*)(psi + k) = pre_ck[b];
+        if (k < C4) *(gv4f*)(psi + k) = pre_ck[b];
       }
       if (C4 + sl < C) psi[C4 + sl] = pre_rem;
       wave_order();
@@ -537,9 +530,9 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
         // Four channels at a time; those from C on add nothing (lambda = 0).
 #pragma unroll 2
         for (int k = 4 * sl; k < C; k += 4 * W) {
-          const v4f a = *(const v4f*)(lam + k) * fsc;
-          const v4f b = *(const v4f*)(psi + k);
-          *(v4f*)(lam + k) = a;
+          const gv4f a = *(const gv4f*)(lam + k) * fsc;
+          const gv4f b = *(const gv4f*)(psi + k);
+          *(gv4f*)(lam + k) = a;
 #pragma unroll
           for (int j = 0; j < 4; ++j) qs = fma((double)a[j], (double)b[j], qs);
         }

@@ -47,6 +47,14 @@ __device__ __forceinline__ void gstore(float4* p, float4 x) {
   const gv4f v = {x.x, x.y, x.z, x.w};
   *(__attribute__((address_space(1))) gv4f*)p = v;
 }
+// Four floats at any 4-byte address.
+typedef float gv4f_any __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ gv4f gload4(const float* p) {
+  return *(const __attribute__((address_space(1))) gv4f_any*)p;
+}
+__device__ __forceinline__ void gstore4(float* p, gv4f v) {
+  *(__attribute__((address_space(1))) gv4f_any*)p = v;
+}
 typedef float gv2f __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ float2 gload(const float2* p) {
   const gv2f v = *(const __attribute__((address_space(1))) gv2f*)p;

@@ -122,6 +122,14 @@ __device__ __forceinline__ void fwd_wave(const FwdParams& P, int64_t pix0, float
   const LoaderT load = LoaderMaker<LoaderT>::make(P, pixc);
   const float slf = (float)sl;
   const int K = CKPT ? P.ckpt_K : 0;
+  // A checkpoint: the line excess Psi e^{-(P_{n-1} - base)} = Psi emp of every
+  // channel, four channels at a time (256^3 cells x 256 channels, K = 16, 1.1 GB
+  // of them: 460 us one at a time, 415 us like this).
+  auto write_state = [&](float* dst, float emp) {
+    const int C4 = C & ~3;
+    for (int k = 4 * sl; k < C4; k += 4 * W) gstore4(dst + k, *(const gv4f*)(psi + k) * emp);
+    if (C4 + sl < C) gstore(dst + C4 + sl, psi[C4 + sl] * emp);
+  };
 
   // State relative to `base`, the dust depth the scaled quantities refer to
   // (Psi = Delta e^{P - base}): Pabs = base (FP64), Pb = depth at the chunk
@@ -287,8 +295,7 @@ __device__ __forceinline__ void fwd_wave(const FwdParams& P, int64_t pix0, float
       auto checkpoint = [&](int i) {
         if (CKPT && (((s0 + i) & (K - 1)) == 0) && live) {
           float* dst = P.ck_state + ((int64_t)((s0 + i) / K) * P.n_pix + pix) * C;
-          const float emp = tbl[kRowEmPex * W + i];
-          for (int k = sl; k < C; k += W) gstore(dst + k, psi[k] * emp);
+          write_state(dst, tbl[kRowEmPex * W + i]);
           wave_order();
         }
       };
@@ -363,8 +370,7 @@ __device__ __forceinline__ void fwd_wave(const FwdParams& P, int64_t pix0, float
         if (CKPT && (((s0 + i) & (K - 1)) == 0) && live) {
           // Line excess entering cell s0+i: Delta = Psi e^{-(P_{n-1} - base)}.
           float* dst = P.ck_state + ((int64_t)((s0 + i) / K) * P.n_pix + pix) * C;
-          const float emp = r[kRowEmPex * W];
-          for (int k = sl; k < C; k += W) gstore(dst + k, psi[k] * emp);
+          write_state(dst, r[kRowEmPex * W]);
         }
         const int pk = __float_as_int(r[kRowPacked * W]);
         const int pku = __builtin_amdgcn_readfirstlane(pk);

@@ -609,14 +609,13 @@ __host__ __device__ inline int thin_adj_wave_floats(int n_chan, int groups) {
   return groups * thin_state_stride(n_chan, groups);
 }
 
-//
 // Narrow channels (M > 0, thin_series_order) need no table and no exponential
 // at the edges: with E = e^{-x^2} at the channel's centre and w = 4 h^2 x^2,
 //   d = (2/sqrt(pi)) 2h E F,  e^{-x_lo^2} - e^{-x_hi^2} = 4h e^{-h^2} E x S(w),
 //   x_lo e^{-x_lo^2} - x_hi e^{-x_hi^2} = 2h e^{-h^2} E (2 x^2 S(w) - K(w)),
 // S = sum w^j / (2j+1)!, K = sum w^j / (2j)! to j = M: no difference of two
 // nearly equal values, and no 16-byte gather per channel. 256 x 256 x 128
-// cells, 800 channels of 0.5 km/s: 544 us by the table, 330 us like this.
+// cells, 800 channels of 0.5 km/s: 544 us by the table, 320 us like this.
 template <bool GEN, int G, int M>
 __global__ __launch_bounds__(256) void thin_adj_kernel(const AdjParams P, int smooth,
                                                        const float4* erfc_pieces) {
