@@ -363,3 +363,17 @@ def test_thin_autograd():
         e = M.err_inf(leaves[f].grad.double().cpu().numpy(), ref[f])
         say(f"      {f}: err_inf {e:.2e}")
         assert e <= TOL_ADJ, (f, e)
+
+
+@pytest.mark.parametrize("dv", [0.509, 0.5092, 1.018, 1.0184])
+def test_channel_means_at_the_edges_of_the_series(dv):
+    # Half a channel just below and above 0.18 and 0.36 of sqrt(2) sigma_turb
+    # (1 km/s): the series to orders 4 and 7, and the erfc pieces beyond. Cold
+    # cells, whose lines are narrowest, and hot ones; lines over both band edges.
+    cube = W.make_cube((3, 5, 70), 2, W.Channels(61, -30.5 * dv, dv), seed=89, v_rms_kms=12.0 * dv)
+    cube.t_kin[:, :, ::3] = 3.0
+    cube.t_kin[:, :, 1::9] = 2.0e4
+    line = line_dict(kappa_dust_cm2g=100.0)
+    check_thin(cube, "f32", "formal", line, label=f"dv={dv}")
+    check_selective(cube, "f32", line, label=f"dv={dv}")
+    check_thin_adjoint(cube, "f32", "formal", line, label=f"dv={dv}", seed=10)
