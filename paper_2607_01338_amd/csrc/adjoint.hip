@@ -63,7 +63,7 @@
 // (which the LDS of the other segments' tables leaves, 19 KB per wavefront at
 // 256 channels): 256^3 cells x 256 channels, FP32, 1660 us by the tables (136
 // vector and 20 LDS instructions per cell and wavefront, two exponentials each
-// way), 960 us like this (87 and 7, two exponentials in all).
+// way), 930 us like this (82 and 6, two exponentials in all).
 
 #include "cell_partials.h"
 #include "cell_setup.h"
@@ -495,49 +495,50 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
       Jcar = __shfl(o.JD, last, 64);
     }
 
-    if (in_regs) {
+    // Every cell of the segment (in every group) within one pass: the pass
+    // loops then need no per-cell bound across groups.
+    bool one_pass = true;
+    if (!in_regs) {
+      for (int i = sl; i < L; i += W)
+        if ((__float_as_int(rows[i * RW + kArPacked]) >> 24) > 1) one_pass = false;
+      one_pass = !__any(!one_pass);
+    }
+    // The two-cell loops below assume a base that does not move.
+    const bool pair = one_pass && !rebased;
+    // Longer segments of such cells: 16 cells at a time, the last first, each
+    // recomputed from the checkpoint. That is half a recompute more at K = 32
+    // and one and a half at K = 64, and still ahead of the tables (256^3 cells
+    // x 256 channels, forward and adjoint: K = 32 2.33 -> 1.55 ms, K = 64 3.56
+    // -> 2.19 ms).
+    const bool in_parts = kReg && !in_regs && pair && K > kAdjReg;
+
+    if (in_regs || in_parts) {
       if constexpr (kReg) {
         // One pass per cell and one base: the cells' rows stay in the lanes
-        // that set them up, the tape (Psi + G, tau_L and 1 - e^{-tau_L} of
-        // every window lane) in registers, so that a cell costs LDS one read
-        // and one write each way. A cell without a window has tau_L = 0, which
-        // leaves the state as it is. The channels from C on (no cotangent,
-        // lambda = 0) start from zero in every segment.
-        if (!pf_ck) load_state(g);
-        psi[C + sl] = 0.f;
-        wave_order();
+        // that set them up (parts: are read back into them), the tape (Psi + G,
+        // tau_L and 1 - e^{-tau_L} of every window lane) in registers, so that
+        // a cell costs LDS one read and one write each way. A cell without a
+        // window has tau_L = 0, which leaves the state as it is. The channels
+        // from C on (no cotangent, lambda = 0) start from zero in every segment.
         auto at = [&](float* base, int k4) { return (float*)((char*)(base + sl) + k4); };
         float pg[kAdjReg], tl[kAdjReg], ab[kAdjReg];
         auto t_of = [&](auto ic) {
           constexpr int i = decltype(ic)::value;
           return (slf + row_bcast<i>(rc.off)) * row_bcast<i>(rc.A);
         };
-        for_each_int(std::make_integer_sequence<int, kAdjReg>{}, [&](auto ic) {
-          constexpr int i = decltype(ic)::value;
-          const float t = t_of(ic);
-          tl[i] = ex2(fmaf(-t, t, row_bcast<i>(rc.lk)));
-          ab[i] = line_absorbed(tl[i]);
-          float* pk = at(psi, row_bcast<i>(rc.k4));
-          const float ps = *pk;
-          pg[i] = ps + row_bcast<i>(rc.G);
-          *pk = fmaf(-pg[i], ab[i], ps);
-          wave_order();
-        });
-        // lambda~ to the base of this segment (as below), and Q at its end
-        // over every channel.
-        const float fsc = Pcar > 0.0 ? (float)exp(-Pcar) : 1.f;
-        double qs = 0.0;
-        // Four channels at a time; those from C on add nothing (lambda = 0).
-#pragma unroll 2
-        for (int k = 4 * sl; k < C; k += 4 * W) {
-          const gv4f a = *(const gv4f*)(lam + k) * fsc;
-          const gv4f b = *(const gv4f*)(psi + k);
-          *(gv4f*)(lam + k) = a;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) qs = fma((double)a[j], (double)b[j], qs);
-        }
-        Qend = row_allsum64(qs);
-        wave_order();
+        // The row of cell 16 part + lane from its table (parts only).
+        auto read_row = [&](int part) {
+          const int i = kAdjReg * part + sl;
+          const float* rw = rows + (i < L ? i : 0) * RW;
+          const int pk = __float_as_int(rw[kArPacked]);
+          rc.np = i < L ? pk >> 24 : 0;
+          rc.A = rc.np ? rw[kArA] : 0.f;
+          rc.off = rc.np ? rw[kArC0] / rc.A : 0.f;
+          rc.G = rc.np ? rw[kArG] : 0.f;
+          rc.lk = rc.np ? rw[kArLk] : -256.f;
+          rc.emlk = rw[kArEmlk];
+          rc.k4 = rc.np ? 4 * (pk & 0xFFFFFF) : 0;
+        };
         auto reverse = [&](auto ic) {
           constexpr int i = decltype(ic)::value;
           const float t = t_of(ic);
@@ -553,28 +554,70 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
           r.s5 = r.s4 * t;
           return r;
         };
-        // Cells 15 .. 0, merged as soon as two (four, eight) are there.
-        RevSums m8[2], m4[2], m2[2];
-        for_each_int(std::make_integer_sequence<int, kAdjReg / 2>{}, [&](auto jc) {
-          constexpr int p = kAdjReg / 2 - 1 - decltype(jc)::value;  // cells 2p + 1, 2p
-          const RevSums odd = reverse(std::integral_constant<int, 2 * p + 1>{});
-          const RevSums even = reverse(std::integral_constant<int, 2 * p>{});
-          m8[p & 1] = row_merge<8>(even, odd);
-          if constexpr (p % 2 == 0) m4[(p >> 1) & 1] = row_merge<4>(m8[0], m8[1]);
-          if constexpr (p % 4 == 0) m2[(p >> 2) & 1] = row_merge<2>(m4[0], m4[1]);
-          if constexpr (p == 0) rsum = row_merge<1>(m2[0], m2[1]);
-        });
+        const int last_part = in_parts ? (L - 1) / kAdjReg : 0;
+        for (int part = last_part; part >= 0; --part) {
+          if (!pf_ck || part != last_part) load_state(g);
+          psi[C + sl] = 0.f;
+          wave_order();
+          for (int p = 0; p <= part; ++p) {
+            if (in_parts) read_row(p);
+            for_each_int(std::make_integer_sequence<int, kAdjReg>{}, [&](auto ic) {
+              constexpr int i = decltype(ic)::value;
+              const float t = t_of(ic);
+              tl[i] = ex2(fmaf(-t, t, row_bcast<i>(rc.lk)));
+              ab[i] = line_absorbed(tl[i]);
+              float* pk = at(psi, row_bcast<i>(rc.k4));
+              const float ps = *pk;
+              pg[i] = ps + row_bcast<i>(rc.G);
+              *pk = fmaf(-pg[i], ab[i], ps);
+              wave_order();
+            });
+          }
+          if (part == last_part) {
+            // lambda~ to the base of this segment (as below), and Q at its end
+            // over every channel.
+            const float fsc = Pcar > 0.0 ? (float)exp(-Pcar) : 1.f;
+            double qs = 0.0;
+            // Four channels at a time; those from C on add nothing (lambda = 0).
+#pragma unroll 2
+            for (int k = 4 * sl; k < C; k += 4 * W) {
+              const gv4f a = *(const gv4f*)(lam + k) * fsc;
+              const gv4f b = *(const gv4f*)(psi + k);
+              *(gv4f*)(lam + k) = a;
+#pragma unroll
+              for (int j = 0; j < 4; ++j) qs = fma((double)a[j], (double)b[j], qs);
+            }
+            Qend = row_allsum64(qs);
+            wave_order();
+          }
+          // Cells 15 .. 0, merged as soon as two (four, eight) are there.
+          RevSums m8[2], m4[2], m2[2];
+          for_each_int(std::make_integer_sequence<int, kAdjReg / 2>{}, [&](auto jc) {
+            constexpr int p = kAdjReg / 2 - 1 - decltype(jc)::value;  // cells 2p + 1, 2p
+            const RevSums odd = reverse(std::integral_constant<int, 2 * p + 1>{});
+            const RevSums even = reverse(std::integral_constant<int, 2 * p>{});
+            m8[p & 1] = row_merge<8>(even, odd);
+            if constexpr (p % 2 == 0) m4[(p >> 1) & 1] = row_merge<4>(m8[0], m8[1]);
+            if constexpr (p % 4 == 0) m2[(p >> 2) & 1] = row_merge<2>(m4[0], m4[1]);
+            if constexpr (p == 0) rsum = row_merge<1>(m2[0], m2[1]);
+          });
+          if (in_parts) {
+            // Lane l of a row holds the sums of the part's cell l with the bits
+            // reversed; none where that cell has no window.
+            const int i = kAdjReg * part + (int)(__builtin_bitreverse32((uint32_t)sl) >> 28);
+            if (i < L) {
+              const bool on = __float_as_int(rows[i * RW + kArPacked]) >> 24 != 0;
+              float* rr = res + i * kAdjRes;
+              rr[kAsS1] = on ? -rsum.s1 : 0.f;
+              rr[kAsS3] = on ? -rsum.s3 : 0.f;
+              rr[kAsS4] = on ? -rsum.s4 : 0.f;
+              rr[kAsS5] = on ? -rsum.s5 : 0.f;
+            }
+            wave_order();
+          }
+        }
       }
     } else {
-      // Every cell of the segment (in every group) within one pass: the pass
-      // loops then need no per-cell bound across groups.
-      bool one_pass = true;
-      for (int i = sl; i < L; i += W)
-        if ((__float_as_int(rows[i * RW + kArPacked]) >> 24) > 1) one_pass = false;
-      one_pass = !__any(!one_pass);
-      // The two-cell loops below assume a base that does not move.
-      const bool pair = one_pass && !rebased;
-
       // lambda~ from the base of the segment above (its start, P_{s1-1}) to the
       // base of this segment's last cell: times e^{-(P_{s1-1} - P_{s0-1} - base)}.
       wave_order();

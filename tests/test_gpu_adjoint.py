@@ -469,3 +469,15 @@ def test_adjoint_register_march(n_los, n_chan, dt, monkeypatch):
         cube.t_kin[0, 0, 20] = 4000.0
     check_adjoint(cube, dt, 16, random_cot(cube.n_pix, n_chan, 12),
                   line=line_dict(kappa_dust_cm2g=20.0), label="register march")
+
+
+@pytest.mark.parametrize("K,n_los,n_chan", [(32, 70, 63), (32, 17, 256), (64, 130, 514)])
+def test_adjoint_register_march_in_parts(K, n_los, n_chan, monkeypatch):
+    # Longer segments go 16 cells at a time: last segments of whole and ragged
+    # parts, cells without the molecule, windows over both band edges.
+    monkeypatch.setenv("IRIS_RT_ADJOINT_SIGHTLINES_PER_WAVE", "4")
+    cube = W.make_cube((3, 3, n_los), 2, W.Channels(n_chan, -0.25 * n_chan, 0.5), seed=98,
+                       v_rms_kms=0.2 * n_chan)
+    cube.x_tracer[:, 1, ::5] = 0.0
+    check_adjoint(cube, "f32", K, random_cot(cube.n_pix, n_chan, 13),
+                  line=line_dict(kappa_dust_cm2g=20.0), label="register march in parts")
