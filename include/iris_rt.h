@@ -481,9 +481,9 @@ typedef struct {
 } iris_levels_config;
 
 /* Grid precomputation ("Grid Precomputation"): solves the OT level balance of
- * `mol` at every node of the (ln n_H2, chi, ln T) grid on the GPU (one
- * wavefront per node, FP64 Gaussian elimination with partial pivoting) and
- * keeps, per node, the population factors of the observed transition per
+ * `mol` at every node of the (ln n_H2, chi, ln T) grid on the GPU (FP64
+ * state reduction; elimination with partial pivoting for a node that cannot
+ * be reduced) and keeps, per node, the population factors of the observed transition per
  * unit tracer density, FU = (g_l/g_u) f_u and FL = f_l - FU, as FP32 pairs
  * [n_chi][n_t][n_n] in device memory owned by the grid. Per-abundance line
  * coefficients follow as j/N = (h nu / 4 pi) A (g_u/g_l) FU and

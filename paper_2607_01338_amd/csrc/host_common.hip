@@ -459,9 +459,10 @@ int adjoint_groups(const iris_fields* f, const iris_channels* ch, const iris_lin
     const double width = 2.0 * std::sqrt((double)c.xw2min) * b * c.inv_dv + 1.0;
     if (plan) {
       // Plans: four sightlines per wavefront up to two passes of their 16
-      // lanes (64-cube batch: every cube at four, 14.1 ms per adjoint phase,
-      // against 15.1 ms with the single-cube rule below and 15.3 ms with the
-      // single-cube tuner's choices).
+      // lanes (64-cube batch, before four sightlines had the register march:
+      // every cube at four, 14.1 ms per adjoint phase, against 15.1 ms with
+      // the single-cube rule below and 15.3 ms with the single-cube tuner's
+      // choices).
       g = width <= 30.0 ? 4 : width <= 60.0 ? 2 : 1;
     } else {
       // The widest packing whose window fits one pass of its lanes. (Which
