@@ -150,12 +150,14 @@ __device__ __forceinline__ CellPartials cell_partials(const Folded& c, double ln
   }
   const double T0 = (double)c.T0;
   const double x = T0 / T;
+  // J = T0 / (e^x - 1): dJ/dT = J^2 e^x / T^2 = J (J + T0) / T^2, which has no
+  // e^x to overflow at low T.
   const double J = T0 / expm1_rare(x);
-  p.dJ_dT = J * J * exp_rare(x) / (T * T);
-  // JL = T0 / (e^y - 1), y = dE/T: dJL/dT = JL^2 e^y dE / (T0 T^2).
+  p.dJ_dT = J * (J + T0) / (T * T);
+  // JL = T0 / (e^y - 1), y = dE/T: dJL/dT = JL (JL + T0) dE / (T0 T^2).
   const double y = dE / T;
   const double JL = T0 / expm1_rare(y);
-  p.dJL_dT = JL * JL * exp_rare(y) * dE / (T0 * T * T);
+  p.dJL_dT = JL * (JL + T0) * dE / (T0 * T * T);
   p.dkL_dlnn = p.dJL_dlnn = 0.0;
   p.line_src = true;
   p.kD_free = (double)c.kD * n;
@@ -177,9 +179,9 @@ __device__ __forceinline__ double planck_rj_dT(const Folded& c, double T) {
     return fmaf(t, fmaf(t, 3.f * qj.w, 2.f * qj.z), qj.y) * (float)kTabPerOctave * du_dT;
   }
   if (!(T > 0.0)) return 0.0;
-  const double x = (double)c.T0 / T;
-  const double J = (double)c.T0 / expm1_rare(x);
-  return J * J * exp_rare(x) / (T * T);
+  const double T0 = (double)c.T0;
+  const double J = T0 / expm1_rare(T0 / T);
+  return J * (J + T0) / (T * T);
 }
 
 

@@ -4,6 +4,7 @@
 #pragma once
 
 #include "device_util.h"
+#include "rare_exp.h"
 
 namespace iris {
 
@@ -244,34 +245,6 @@ __device__ __forceinline__ bool tab_coord(float T, int& idx, float& t) {
 __device__ __forceinline__ float tab_eval(const Folded& c, int which, int idx, float t) {
   const gv4f q = gload_at<gv4f>(c.tab, (uint32_t)((which * kTabN + idx) * 16));
   return fmaf(t, fmaf(t, fmaf(t, q.w, q.z), q.y), q.x);
-}
-
-// Exponentials of the rare cells outside the tables, FP64 to a few ulp:
-// e^x = (1 + p) 2^n, |x - n ln 2| <= ln 2 / 2, p from the exponential series.
-// A loop on purpose: the polynomial constants of an unrolled exponential would
-// be kept in registers throughout the march (about 20 of them, a wavefront per
-// SIMD less).
-struct ExpParts {
-  double p;
-  int n;
-};
-__device__ __forceinline__ ExpParts exp_parts(double x) {
-  const double xc = fmin(fmax(x, -2000.0), 2000.0);
-  const double n = rint(xc * 1.44269504088896340736);
-  double r = fma(n, -0x1.62e42fep-1, xc);  // ln 2: 28 bits, then the rest
-  r = fma(n, -0x1.f473de6af278fp-30, r);
-  double s = 1.0;
-#pragma unroll 1
-  for (int k = 16; k >= 2; --k) s = fma(r / (double)k, s, 1.0);
-  return {r * s, (int)n};
-}
-__device__ __forceinline__ double exp_rare(double x) {
-  const ExpParts e = exp_parts(x);
-  return ldexp(1.0 + e.p, e.n);
-}
-__device__ __forceinline__ double expm1_rare(double x) {
-  const ExpParts e = exp_parts(x);
-  return ldexp(e.p, e.n) + (ldexp(1.0, e.n) - 1.0);
 }
 
 // Direct evaluation (FP64) for temperatures outside the tables.

@@ -481,3 +481,31 @@ def test_adjoint_register_march_in_parts(K, n_los, n_chan, monkeypatch):
     cube.x_tracer[:, 1, ::5] = 0.0
     check_adjoint(cube, "f32", K, random_cot(cube.n_pix, n_chan, 13),
                   line=line_dict(kappa_dust_cm2g=20.0), label="register march in parts")
+
+
+@pytest.mark.parametrize("K", [8, 16])
+@pytest.mark.parametrize("field", ["t_kin", "t_dust"])
+def test_adjoint_cold_cells(field, K):
+    # Down to a thousandth of a kelvin, where e^{T0/T} overflows and the source
+    # function and its slope vanish. (The oracle's own slope is 0 x infinity
+    # there: those cells' temperature gradients are compared with zero.)
+    cube = W.make_cube((2, 5, 70), 2, W.Channels(64, -16.0, 0.5), seed=83, v_rms_kms=4.0,
+                       t_dust=field == "t_dust")
+    t = getattr(cube, field).reshape(-1)
+    t[::5] = np.geomspace(1e-3, 0.3, t[::5].size)
+    say(f"[adj] cold {field}, K={K}")
+    dev = to_device(cube, "f32")
+    cot = random_cot(cube.n_pix, 64, 14)
+    _, g = gpu_grad(cube, dev, cot, K)
+    ref = oracle.adjoint(problem(cube, dequantised(dev)), W.LINE_13CO_21,
+                         {k: v.astype(np.float64) for k, v in cot.items()})
+    for f in FIELDS + (("t_dust",) if field == "t_dust" else ()):
+        r = ref[f]
+        if f == field:
+            none = np.isnan(r)
+            assert 0 < none.sum() < t[::5].size and np.all(getattr(cube, field)[none] < 0.0152)
+            r = np.where(none, 0.0, r)
+        assert np.all(np.isfinite(g[f])), f
+        e = M.err_inf(g[f], r)
+        say(f"      {f}: err_inf {e:.2e}")
+        assert e <= TOL_ADJ, (f, e)

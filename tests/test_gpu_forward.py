@@ -366,3 +366,21 @@ def test_temperatures_outside_the_tables():
     for k in "TCDLB":
         e = M.err_inf(res[k].double().cpu().numpy(), ref[k])
         assert e <= TOL_FWD, (k, e)
+
+
+@pytest.mark.parametrize("mode", [("formal", "thick"), ("smooth", "thick"), ("formal", "thin")])
+@pytest.mark.parametrize("field", ["t_kin", "t_dust"])
+def test_cold_cells(field, mode):
+    # Down to a thousandth of a kelvin, where e^{T0/T} overflows: no emission.
+    cube = W.make_cube((2, 5, 70), 2, W.Channels(64, -16.0, 0.5), seed=82, v_rms_kms=4.0,
+                       t_dust=field == "t_dust")
+    t = getattr(cube, field).reshape(-1)
+    t[::5] = np.geomspace(1e-3, 0.3, t[::5].size)
+    say(f"[fwd] cold {field}, {mode}")
+    dev = to_device(cube, "f32")
+    line = line_dict(integrator=mode[0], transfer=mode[1])
+    res = gpu_forward(cube, dev, line)
+    ref = oracle.forward(problem(cube, dequantised(dev)), line)
+    for k in "TCDLB":
+        e = M.err_inf(res[k].double().cpu().numpy(), ref[k])
+        assert e <= TOL_FWD, (k, e)
