@@ -516,12 +516,15 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
       if constexpr (kReg) {
         // One pass per cell and one base: the cells' rows stay in the lanes
         // that set them up (parts: are read back into them), the tape (Psi + G,
-        // tau_L and 1 - e^{-tau_L} of every window lane) in registers, so that
-        // a cell costs LDS one read and one write each way. A cell without a
-        // window has tau_L = 0, which leaves the state as it is. The channels
-        // from C on (no cotangent, lambda = 0) start from zero in every segment.
+        // tau_L, e^{-tau_L} and 1 - e^{-tau_L} of every window lane) in
+        // registers, so that a cell costs LDS one read and one write each way.
+        // Both of the last two, since either found from the other loses its
+        // relative accuracy: from a depth of 17 on, 1 - (1 - e^{-tau}) leaves
+        // nothing of the cotangent behind the line. A cell without a window has
+        // tau_L = 0, which leaves the state as it is. The channels from C on (no
+        // cotangent, lambda = 0) start from zero in every segment.
         auto at = [&](float* base, int k4) { return (float*)((char*)(base + sl) + k4); };
-        float pg[kAdjReg], tl[kAdjReg], ab[kAdjReg];
+        float pg[kAdjReg], tl[kAdjReg], E[kAdjReg], ab[kAdjReg];
         auto t_of = [&](auto ic) {
           constexpr int i = decltype(ic)::value;
           return (slf + row_bcast<i>(rc.off)) * row_bcast<i>(rc.A);
@@ -544,7 +547,7 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
           const float t = t_of(ic);
           float* lk = at(lam, row_bcast<i>(rc.k4));
           const float lt = *lk;
-          const float le = fmaf(-lt, ab[i], lt);
+          const float le = lt * E[i];
           *lk = le;
           wave_order();
           RevSums r;  // all but the sign
@@ -565,6 +568,7 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
               constexpr int i = decltype(ic)::value;
               const float t = t_of(ic);
               tl[i] = ex2(fmaf(-t, t, row_bcast<i>(rc.lk)));
+              E[i] = ex2(-tl[i]);
               ab[i] = line_absorbed(tl[i]);
               float* pk = at(psi, row_bcast<i>(rc.k4));
               const float ps = *pk;
