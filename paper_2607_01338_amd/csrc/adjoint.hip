@@ -92,9 +92,9 @@ constexpr int kAdjRowGen = 16;
 enum : int { kArH = 12, kArKd, kArEk };
 // Result: the window sums of the reverse pass (lambda (E - 1), the
 // taubar-weighted profile moments and, with separate source functions, the
-// h and kD sums), then the cell's stored fields (ln n, T, X, T_dust) for the
-// chain rule.
-enum : int { kAsS1 = 0, kAsS3, kAsS4, kAsS5, kAsSH, kAsSK, kAsLnn = 8, kAsT, kAsX, kAsTd };
+// h and kD sums), then the cell's profile offset m (register march by parts) and
+// its stored fields (ln n, T, X, T_dust) for the chain rule.
+enum : int { kAsS1 = 0, kAsS3, kAsS4, kAsS5, kAsSH, kAsSK, kAsM, kAsLnn = 8, kAsT, kAsX, kAsTd };
 
 // 1 - 2^{-x} for x >= 0, with the formal step's series below kSeriesX.
 __device__ __forceinline__ float one_minus_ex2_neg(float x) {
@@ -209,9 +209,9 @@ struct AdjLoaderMaker<DynLoader> {
 
 // What a lane keeps of the cell it set up in the register march.
 struct RegCell {
-  // Profile and state row: the profile argument is A (lane + off), the depth
+  // Profile and state row: the profile argument is A (lane + m), the depth
   // zero without a window.
-  float G, A, off, lk, emlk;
+  float G, A, m, lk, emlk;
   int k4, np;                // byte offset of the window's first channel, passes (0 or 1)
   float omen, epex, Bm;
   double an;
@@ -447,7 +447,7 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
         in_regs = true;
         rc.G = np ? (float)Gn : 0.f;
         rc.A = np ? o.A : 0.f;
-        rc.off = np ? o.c0 / o.A : 0.f;
+        rc.m = np ? o.m : 0.f;
         rc.lk = np ? o.lk : -256.f;
         rc.emlk = ex2(-o.lk);
         rc.k4 = np ? 4 * o.kstart : 0;
@@ -478,6 +478,7 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
           rw[kArEk] = ex2((valid ? o.kD : 0.f) * kLog2e);
         }
         float* rr = res + i * kAdjRes;
+        if (kReg) rr[kAsM] = o.m;
         rr[kAsLnn] = in.lnn;
         rr[kAsT] = in.T;
         rr[kAsX] = in.X;
@@ -527,7 +528,7 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
         float pg[kAdjReg], tl[kAdjReg], E[kAdjReg], ab[kAdjReg];
         auto t_of = [&](auto ic) {
           constexpr int i = decltype(ic)::value;
-          return (slf + row_bcast<i>(rc.off)) * row_bcast<i>(rc.A);
+          return (slf + row_bcast<i>(rc.m)) * row_bcast<i>(rc.A);
         };
         // The row of cell 16 part + lane from its table (parts only).
         auto read_row = [&](int part) {
@@ -536,7 +537,7 @@ __device__ __forceinline__ void adj_wave(const AdjParams& P, int64_t pix0, float
           const int pk = __float_as_int(rw[kArPacked]);
           rc.np = i < L ? pk >> 24 : 0;
           rc.A = rc.np ? rw[kArA] : 0.f;
-          rc.off = rc.np ? rw[kArC0] / rc.A : 0.f;
+          rc.m = rc.np ? res[(i < L ? i : 0) * kAdjRes + kAsM] : 0.f;
           rc.G = rc.np ? rw[kArG] : 0.f;
           rc.lk = rc.np ? rw[kArLk] : -256.f;
           rc.emlk = rw[kArEmlk];

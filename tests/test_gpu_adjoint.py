@@ -559,3 +559,31 @@ def test_adjoint_behind_an_opaque_line(groups, K, monkeypatch):
         e = np.abs(g[f][behind] / ref[f][behind] - 1.0).max(axis=2)
         say(f"      {f}: relative error per cell, by depth {e.ravel()}")
         assert e.max() <= 1e-4, (f, e)
+
+
+@pytest.mark.parametrize("K", [16, 32])
+def test_adjoint_register_march_is_as_accurate_as_the_tables(K, monkeypatch):
+    # Thin cells seen in the wings of their line, where the profile's relative
+    # error is 2 t times that of its argument t: root mean square over the
+    # cells, four sightlines per wavefront (the register march) against one.
+    line = line_dict(kappa_dust_cm2g=1e-6)
+    n_chan = 33
+    cube = W.make_cube((8, 8, 64), 2, W.Channels(n_chan, -16.5, 1.0), seed=100, v_rms_kms=0.0)
+    rng = np.random.default_rng(6)
+    cube.ln_nh2[...] = np.log(1e3)
+    cube.t_kin[...] = rng.uniform(20.0, 100.0, cube.t_kin.shape)
+    cube.v_los[...] = rng.uniform(-5.0, 5.0, cube.v_los.shape)
+    cube.x_tracer[...] = 1e-9
+    dev = to_device(cube, "f64")
+    cot = {"L": np.zeros((64, n_chan), dtype=np.float32)}
+    cot["L"][:, n_chan // 2] = 1.0
+    ref = oracle.adjoint(problem(cube, dequantised(dev)), line,
+                         {k: v.astype(np.float64) for k, v in cot.items()})
+    # Within the window (4.5 Doppler widths at least) of every cell.
+    rms = {}
+    for groups in (1, 4):
+        monkeypatch.setenv("IRIS_RT_ADJOINT_SIGHTLINES_PER_WAVE", str(groups))
+        _, g = gpu_grad(cube, dev, cot, K, line)
+        rms[groups] = [np.sqrt(np.mean((g[f] / ref[f] - 1.0) ** 2)) for f in ("x_tracer", "v_los")]
+    say(f"[adj] wings, K={K}: rms relative error {rms}")
+    assert np.all(np.array(rms[4]) <= 1.1 * np.array(rms[1]))
