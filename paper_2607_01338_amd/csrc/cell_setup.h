@@ -414,13 +414,16 @@ __device__ __forceinline__ CellOut cell_setup(const Folded& c, const CellIn& in,
 // exponential is under 2e-6 of the step; the subtraction is exact while
 // 2^{-x} >= 1/2).
 constexpr float kSeriesX = 0.044f;
-__device__ __forceinline__ float line_absorbed(float x) {  // 1 - e^{-tau}
-  float q = fmaf(x, 0.0555041087f, -0.2402265070f);  // (ln 2)^3/6, -(ln 2)^2/2
+constexpr float kSeriesC2 = -0.2402265070f;  // -(ln 2)^2/2
+// 1 - e^{-tau}; a caller may hold the series' second constant in a register.
+__device__ __forceinline__ float line_absorbed(float x, float c2 = kSeriesC2) {
+  float q = fmaf(x, 0.0555041087f, c2);  // (ln 2)^3/6
   q = fmaf(x, q, 0.6931471806f);                      // ln 2
   return x < kSeriesX ? x * q : 1.f - ex2(-x);
 }
-__device__ __forceinline__ float formal_line_step(float ps, float g, float x) {
-  return fmaf(-(ps + g), line_absorbed(x), ps);
+__device__ __forceinline__ float formal_line_step(float ps, float g, float x,
+                                                  float c2 = kSeriesC2) {
+  return fmaf(-(ps + g), line_absorbed(x, c2), ps);
 }
 
 // A step whose depth is at most kFaintTau everywhere in the window needs no

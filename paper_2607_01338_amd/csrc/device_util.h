@@ -215,8 +215,13 @@ __device__ __forceinline__ float wave_sum_dpp(float x) {
 
 // Sum within aligned groups of W = 16, 32 or 64 lanes, FP32, result in every
 // lane of the group: a cyclic butterfly of row rotations inside each row of
-// 16 (DPP), then a lane swizzle across the two rows of a 32-lane half, then
-// the two halves for W = 64.
+// 16 (DPP), then across the rows. Over 64 lanes the rows and then the halves are
+// brought together by lane swaps: with an LDS swizzle and lane reads into scalar
+// registers, several sums in a row were scheduled one after the other, an LDS
+// round trip each (adjoint of 256 x 256 x 64 cells, 256 channels of 0.3 km/s,
+// K = 16 and 64: 1060 and 1440 us like that, 995 and 1365 us like this). Over 32
+// lanes, where they overlap, the swizzle is the faster (K = 16 at 0.5 km/s 652
+// against 665 us).
 constexpr int kDppRowRor = 0x120;
 template <int W>
 __device__ __forceinline__ float group_allsum(float x) {
@@ -225,14 +230,18 @@ __device__ __forceinline__ float group_allsum(float x) {
   x += dpp_f32<kDppRowRor + 4, 0xF>(x);
   x += dpp_f32<kDppRowRor + 2, 0xF>(x);
   x += dpp_f32<kDppRowRor + 1, 0xF>(x);
-  if (W >= 32) {
+  if (W == 32) {
     // Bit-mask swizzle inside 32 lanes: and 0x1F, or 0, xor 0x10.
     x += __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(x), 0x401F));
   }
   if (W == 64) {
-    const int xi = __float_as_int(x);
-    x = __int_as_float(__builtin_amdgcn_readlane(xi, 0)) +
-        __int_as_float(__builtin_amdgcn_readlane(xi, 32));
+    // Each swap leaves one of the two rows (halves) in both, in either result.
+    const uint32_t u = __float_as_uint(x);
+    const auto row = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    x = __uint_as_float(row[0]) + __uint_as_float(row[1]);
+    const uint32_t v = __float_as_uint(x);
+    const auto half = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    x = __uint_as_float(half[0]) + __uint_as_float(half[1]);
   }
   return x;
 }
