@@ -106,9 +106,15 @@ constexpr int kBeamFusedRadius = 12;
 constexpr int kBeamCh = 32;     // channels of a workgroup
 constexpr int kBeamPerWave = 8;  // positions along n2 per wavefront
 
+// Wavefronts per SIMD that the window leaves: 2R + 1 rows of four FP32 sums
+// (88, 124, 158 and 182 registers at R = 4, 7, 10 and 12).
+__host__ __device__ constexpr int beam_waves(int R) {
+  return R <= 4 ? 5 : R <= 7 ? 4 : R <= 10 ? 3 : 2;
+}
+
 template <int R>
-__global__ __launch_bounds__(512) void beam_fused_kernel(const BeamArgs a, int seg_rows,
-                                                         int n_seg) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(beam_waves(R)))) void
+beam_fused_kernel(const BeamArgs a, int n_seg) {
   constexpr int kTaps = 2 * R + 1;
   extern __shared__ float rows[];  // [2][(positions + 2R)][kBeamCh]
   const int nw = (int)(blockDim.x >> 6);
@@ -124,7 +130,8 @@ __global__ __launch_bounds__(512) void beam_fused_kernel(const BeamArgs a, int s
   const int ch = lane % kBeamCh, c = cb * kBeamCh + ch;
   const bool in_c = c < C;
   const int run = wave * kBeamPerWave + 4 * (lane / kBeamCh);  // first position of the lane's run
-  const int m0 = seg * seg_rows, m1 = min(m0 + seg_rows, n1);
+  // Segments differ by one row at most.
+  const int m0 = (int)((int64_t)n1 * seg / n_seg), m1 = (int)((int64_t)n1 * (seg + 1) / n_seg);
 
   float w[R + 1];
 #pragma unroll
@@ -141,38 +148,47 @@ __global__ __launch_bounds__(512) void beam_fused_kernel(const BeamArgs a, int s
     for (int k = 0; k < kRounds; ++k) {
       if (k * hs >= held) break;  // wider workgroups take fewer rounds
       const int h = h0 + k * hs, p2 = p2_0 - R + h;
-      const bool in = h < held && in_c && p2 >= 0 && p2 < n2 && row >= 0 && row < n1;
+      const bool in = h < held && in_c && p2 >= 0 && p2 < n2;
       pre[k] = in ? gload(a.in + ((int64_t)row * n2 + p2) * C + c) : 0.f;
     }
   };
-  fetch(m0 - R);
-  for (int row = m0 - R, b = 0; row < m1 + R; ++row, b ^= 1) {
-    float* buf = rows + b * held * kBeamCh;
-#pragma unroll
-    for (int k = 0; k < kRounds; ++k) {
-      if (k * hs >= held) break;
-      const int h = h0 + k * hs;
-      if (h < held) buf[h * kBeamCh + ch] = pre[k];
-    }
-    __syncthreads();  // also: the reads of this buffer two rows ago are done
-    if (row + 1 < m1 + R) fetch(row + 1);
-    float v[4] = {};
-#pragma unroll
-    for (int j = 0; j < 4 + 2 * R; ++j) {
-      const float x = buf[(run + j) * kBeamCh + ch];
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        const int d = j - R - m < 0 ? m + R - j : j - R - m;
-        if (d <= R) v[m] = fmaf(w[d], x, v[m]);
-      }
-    }
+  // Rows before the map add nothing; those beyond it only move the window on.
+  const int first = max(m0 - R, 0);
+  fetch(first);
+  for (int row = first, b = 0; row < m1 + R; ++row, b ^= 1) {
     // acc[k] is output row row - R + k after the shift: distance |R - k|.
+    if (row < n1) {
+      float* buf = rows + b * held * kBeamCh;
 #pragma unroll
-    for (int k = 0; k < kTaps; ++k) {
-      const float wk = w[k < R ? R - k : k - R];
+      for (int k = 0; k < kRounds; ++k) {
+        if (k * hs >= held) break;
+        const int h = h0 + k * hs;
+        if (h < held) buf[h * kBeamCh + ch] = pre[k];
+      }
+      __syncthreads();  // also: the reads of this buffer two rows ago are done
+      if (row + 1 < min(m1 + R, n1)) fetch(row + 1);
+      float v[4] = {};
 #pragma unroll
-      for (int m = 0; m < 4; ++m)
-        acc[k][m] = fmaf(wk, v[m], k + 1 < kTaps ? acc[k + 1][m] : 0.f);
+      for (int j = 0; j < 4 + 2 * R; ++j) {
+        const float x = buf[(run + j) * kBeamCh + ch];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          const int d = j - R - m < 0 ? m + R - j : j - R - m;
+          if (d <= R) v[m] = fmaf(w[d], x, v[m]);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < kTaps; ++k) {
+        const float wk = w[k < R ? R - k : k - R];
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+          acc[k][m] = fmaf(wk, v[m], k + 1 < kTaps ? acc[k + 1][m] : 0.f);
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k + 1 < kTaps; ++k)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) acc[k][m] = acc[k + 1][m];
     }
     const int o = row - R;
     if (o >= m0 && in_c) {
@@ -185,24 +201,32 @@ __global__ __launch_bounds__(512) void beam_fused_kernel(const BeamArgs a, int s
 }
 
 // Workgroups of the fused kernel: the positions along n2 in equal tiles of at
-// most 64, and as many segments of n1 as stay resident together (four
-// wavefronts per SIMD up to R = 7, two beyond, by registers), none shorter
-// than four rows. A row costs a workgroup 0.6 + 0.08 R us on an idle device
-// and the halo's rows as much as the segment's own, so small maps want many
-// short segments (80 x 50 x 127, R = 7: 61 us in segments of 27 rows, 21 us in
-// segments of 4).
+// most 64, and segments of n1, as many as stay resident together (a few more and
+// the rest is a second round: 378 x 156 x 222, R = 11, 151 us by a count that
+// overlooked whole workgroups, 83 us like this; a workgroup of more than four
+// wavefronts puts two on one SIMD). A row costs a workgroup 0.6 + 0.08 R us on an
+// idle device and the halo's rows as much as the segment's own, so small maps
+// want many short segments (80 x 50 x 127, R = 7: 61 us in segments of 27 rows,
+// 21 us in segments of 4). Where several workgroups share a CU, four rows are the
+// shortest that pay (312 x 65 x 84, R = 5: 17 us in segments of four rows, 27 us
+// of two); up to one workgroup a CU, one row (31 x 50 x 127, R = 6: 18.6 us in
+// segments of five rows, 14.8 us of one).
 struct BeamSplit {
-  int nw = 0, seg_rows = 0;
+  int nw = 0, segs = 0, seg_rows = 0;
   int64_t cols = 0;
 };
 BeamSplit beam_split(const BeamArgs& a) {
+  constexpr int64_t kCUs = 256;
   BeamSplit s;
   const int64_t tiles = (a.n2 + 63) / 64;
   s.nw = (int)(((a.n2 + tiles - 1) / tiles + kBeamPerWave - 1) / kBeamPerWave);
   s.cols = tiles * ((a.C + kBeamCh - 1) / kBeamCh);
-  const int64_t resident = (a.R <= 7 ? 4096 : 2048) / s.nw;
-  const int64_t segs = std::max<int64_t>(1, std::min<int64_t>(resident / s.cols, a.n1 / 4));
-  s.seg_rows = (int)((a.n1 + segs - 1) / segs);
+  const int waves = beam_waves(a.R);
+  const int64_t resident = kCUs * (s.nw > 4 ? waves / 2 : 4 * waves / s.nw) / s.cols;
+  const int64_t want = std::max<int64_t>(a.n1 / 4, std::min<int64_t>(a.n1, kCUs / s.cols));
+  const int64_t most = std::max<int64_t>(1, std::min<int64_t>(resident, want));
+  s.seg_rows = (int)((a.n1 + most - 1) / most);
+  s.segs = (int)((a.n1 + s.seg_rows - 1) / s.seg_rows);
   return s;
 }
 
@@ -210,10 +234,9 @@ template <int R>
 int launch_beam_fused(const BeamArgs& a, const BeamSplit& s, hipStream_t st) {
   if constexpr (R > 1)
     if (a.R < R) return launch_beam_fused<R - 1>(a, s, st);
-  const int n_seg = (int)((a.n1 + s.seg_rows - 1) / s.seg_rows);
   const size_t lds = (size_t)2 * (s.nw * kBeamPerWave + 2 * R) * kBeamCh * sizeof(float);
-  hipLaunchKernelGGL(beam_fused_kernel<R>, dim3((unsigned)(s.cols * n_seg)), dim3(64 * s.nw), lds,
-                     st, a, s.seg_rows, n_seg);
+  hipLaunchKernelGGL(beam_fused_kernel<R>, dim3((unsigned)(s.cols * s.segs)), dim3(64 * s.nw), lds,
+                     st, a, s.segs);
   return (int)hipGetLastError();
 }
 
@@ -361,14 +384,19 @@ iris_status iris_beam_convolve(const float* cube, float* out, int32_t n1, int32_
   // fill the registers beyond); it reads neighbours of what it writes, so an
   // output that overlaps the cube takes the two passes. So do wide beams on
   // maps that leave it short segments, mostly halo: from R = 7 with rows that
-  // the passes load four channels at a time (148 x 96 x 468, segments of 7
-  // rows at R = 7: 55 us against 50; of 14 at R = 10: 94 against 63), from
-  // R = 8 with others (358 x 56 x 187, 8 rows at R = 10: 77 against 73; 449 x
-  // 138 x 74, 13 rows: 92 against 92; 203 x 70 x 446, 15 rows: 97 against 116).
+  // the passes load four channels at a time (148 x 96 x 468: segments of 9 rows
+  // at R = 9, 74 us against 58; 208 x 74 x 260: of 15 at R = 10, 54 against 47;
+  // 148 x 96 x 468: of 19 at R = 11, 64 against 66), from R = 8 with others (396
+  // x 89 x 62, 4 rows at R = 9: 60 against 52; 207 x 91 x 255, 7 rows at R = 8:
+  // 57 against 82). And so do strips of up to four positions, which leave half of
+  // the smallest tile idle, under beams wider than they are, once they fill the
+  // device (1065 x 4 x 1280, R = 6: 37 against 31; 243 x 3 x 2661, R = 3: 16
+  // against 21).
   const BeamSplit split = beam_split(a);
-  const bool short_segs = v4 ? a.R >= 7 && 2 * split.seg_rows < 3 * a.R
-                             : a.R >= 8 && split.seg_rows < a.R;
-  if (a.R <= kBeamFusedRadius && !short_segs && !overlap(cube, out, need)) {
+  const bool short_segs = v4 ? a.R >= 7 && 2 * split.seg_rows <= 3 * a.R
+                             : a.R >= 8 && 4 * split.seg_rows < 3 * a.R;
+  const bool strip = n2 <= kBeamPerWave / 2 && a.R > n2 && split.cols * split.segs > 256;
+  if (a.R <= kBeamFusedRadius && !short_segs && !strip && !overlap(cube, out, need)) {
     a.in = cube;
     a.out = out;
     return host::hip_status(launch_beam_fused<kBeamFusedRadius>(a, split, st), "beam kernel");

@@ -104,3 +104,20 @@ def test_beam_and_lv_of_a_synthesised_cube():
     ref_beam = post.beam_convolve(Lh, 2.39)
     assert M.err_inf(beam.double().cpu().numpy(), ref_beam) <= TOL_FWD
     assert M.err_inf(lv.double().cpu().numpy(), post.lv_mean(ref_beam, 1)) <= TOL_FWD
+
+
+@pytest.mark.parametrize("shape,fwhm", [((3, 5, 2), 3.0), ((31, 50, 127), 3.0), ((12, 20, 9), 2.9),
+                                        ((150, 3, 700), 2.3), ((150, 4, 700), 1.2),
+                                        ((83, 130, 233), 4.5), ((101, 61, 64), 1.9)])
+def test_beam_segments(shape, fwhm):
+    # Maps shorter than the window, segments of one row and of unequal lengths,
+    # strips of up to four positions on either side of the rule.
+    say(f"[beam] shape={shape} fwhm={fwhm}")
+    a = _rand_cube(shape, 6)
+    t = torch.from_numpy(a).cuda()
+    out = rt.beam_convolve(t, fwhm)
+    two = rt.beam_convolve(t, fwhm, out=t)
+    torch.cuda.synchronize()
+    assert torch.equal(out, two)
+    assert M.err_inf(out.double().cpu().numpy(),
+                     post.beam_convolve(a.astype(np.float64), fwhm)) <= TOL_FWD
