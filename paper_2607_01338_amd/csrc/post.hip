@@ -261,7 +261,7 @@ __global__ __launch_bounds__(64 * kLvMaxParts) void lv_mean_kernel(const float* 
   T* out = (T*)outp;
   const int lane = (int)(threadIdx.x & 63), p = (int)(threadIdx.x >> 6);
   const int parts = (int)(blockDim.x >> 6);
-  const int64_t e = (int64_t)blockIdx.x * 64 + lane;
+  const int64_t e = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 64 + lane;
   double acc[V] = {};
   if (e < total) {
     const int64_t o = e / nv, k = e % nv;
@@ -317,8 +317,10 @@ int launch_lv_mean(const float* cube, float* out, int64_t n1, int64_t n2, int64_
   // eight loads each.
   int64_t parts = std::min<int64_t>((4096 + blocks - 1) / blocks, n_axis / 8);
   parts = std::max<int64_t>(1, std::min<int64_t>(parts, kLvMaxParts));
-  hipLaunchKernelGGL(lv_mean_kernel<V>, dim3((unsigned)blocks), dim3((unsigned)(64 * parts)), 0, st,
-                     cube, out, n1, n2, C, axis);
+  // A grid axis holds less than 2^32 threads: rows of at most 2^20 workgroups.
+  const int64_t bx = std::min<int64_t>(blocks, 1 << 20), by = (blocks + bx - 1) / bx;
+  hipLaunchKernelGGL(lv_mean_kernel<V>, dim3((unsigned)bx, (unsigned)by),
+                     dim3((unsigned)(64 * parts)), 0, st, cube, out, n1, n2, C, axis);
   return (int)hipGetLastError();
 }
 
@@ -396,7 +398,11 @@ iris_status iris_beam_convolve(const float* cube, float* out, int32_t n1, int32_
   const bool short_segs = v4 ? a.R >= 7 && 2 * split.seg_rows <= 3 * a.R
                              : a.R >= 8 && 4 * split.seg_rows < 3 * a.R;
   const bool strip = n2 <= kBeamPerWave / 2 && a.R > n2 && split.cols * split.segs > 256;
-  if (a.R <= kBeamFusedRadius && !short_segs && !strip && !overlap(cube, out, need)) {
+  // The fused kernel's row and position numbers fit 32 bits, and a launch takes
+  // less than 2^32 threads: maps of more positions than that go in two passes.
+  const bool fits = a.n1 <= 0x7FFFFFFF - kBeamFusedRadius &&
+                    split.cols * split.segs * split.nw * 64 < (1ll << 32);
+  if (a.R <= kBeamFusedRadius && fits && !short_segs && !strip && !overlap(cube, out, need)) {
     a.in = cube;
     a.out = out;
     return host::hip_status(launch_beam_fused<kBeamFusedRadius>(a, split, st), "beam kernel");
@@ -430,8 +436,6 @@ iris_status iris_lv_mean(const float* cube, float* out, int32_t n1, int32_t n2, 
   if (s != IRIS_OK) return s;
   if (axis != 0 && axis != 1) return host::fail(IRIS_E_INVALID_ARG, "axis must be 0 or 1");
   const bool v4 = aligned4(cube, n_chan) && aligned4(out, n_chan);
-  const int64_t blocks = ((axis == 0 ? n2 : n1) * ((int64_t)n_chan / (v4 ? 4 : 1)) + 63) / 64;
-  if (blocks > 0x7FFFFFFF) return host::fail(IRIS_E_UNSUPPORTED, "cube too large for one launch");
   const hipStream_t st = (hipStream_t)stream;
   return host::hip_status(v4 ? launch_lv_mean<4>(cube, out, n1, n2, n_chan, axis, st)
                              : launch_lv_mean<1>(cube, out, n1, n2, n_chan, axis, st),

@@ -121,3 +121,38 @@ def test_beam_segments(shape, fwhm):
     assert torch.equal(out, two)
     assert M.err_inf(out.double().cpu().numpy(),
                      post.beam_convolve(a.astype(np.float64), fwhm)) <= TOL_FWD
+
+
+def test_beam_of_more_positions_than_one_launch_has_threads():
+    # A strip of 2^29 positions and one channel, eight lanes a position in one
+    # kernel: 2^32 threads.
+    n = (1 << 29) + 5
+    t = torch.empty((1, n, 1), device="cuda")
+    ends = [(0, 4096), (n - 4096, n)]
+    rng = np.random.default_rng(7)
+    for lo, hi in ends:
+        t[0, lo:hi, 0] = torch.from_numpy(rng.standard_normal(hi - lo).astype(np.float32)).cuda()
+    say(f"[beam] {n} positions")
+    out = rt.beam_convolve(t, 1.0)
+    torch.cuda.synchronize()
+    for lo, hi in ends:
+        ref = post.beam_convolve(t[:, lo:hi].double().cpu().numpy(), 1.0)[0, :, 0]
+        got = out[0, lo:hi, 0].double().cpu().numpy()
+        # The window's inner edge lacks its neighbours.
+        keep = slice(0, -2) if lo == 0 else slice(2, None)
+        assert M.err_inf(got[keep], ref[keep]) <= TOL_FWD
+
+
+def test_lv_mean_of_more_columns_than_one_launch_has_threads():
+    # 2^32 columns and some (17 GB of them): the mean of a single row is the row.
+    n2, c = (1 << 22) + 3, 1025
+    t = torch.empty((1, n2, c), device="cuda")
+    flat = t.view(-1)
+    spans = [(0, 5000), ((1 << 32) - 5000, (1 << 32) + 5000), (flat.numel() - 5000, flat.numel())]
+    for lo, hi in spans:
+        flat[lo:hi] = torch.arange(hi - lo, device="cuda", dtype=torch.float32) + 0.5
+    say(f"[lv] {n2} x {c} columns")
+    out = rt.lv_mean(t, 0).view(-1)
+    torch.cuda.synchronize()
+    for lo, hi in spans:
+        assert torch.equal(out[lo:hi], flat[lo:hi])
