@@ -187,8 +187,7 @@ __attribute__((amdgpu_waves_per_eu(NL <= 48 ? 4 : 3))) void ot_reduce_kernel(con
   __shared__ double base[NL * NL], coll[NL * NL];
   const int L = P.L;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int pair = blockIdx.x / P.splits, split = blockIdx.x % P.splits;
-  const int i_t = pair % P.n_t, i_c = pair / P.n_t;
+  const int i_t = blockIdx.x / P.splits, split = blockIdx.x % P.splits, i_c = blockIdx.y;
   const double chi = P.chi0 + i_c * P.dchi;
   const double T = exp(P.lnt0 + i_t * P.dlnt);
   ot_rates<NL>(P, T, chi, base, coll);
@@ -295,8 +294,7 @@ __attribute__((amdgpu_waves_per_eu(NL <= 24 ? 4 : NL <= 32 ? 3 : 2))) void ot_re
   __shared__ double base[NL * NS], coll[NL * NS];
   const int L = P.L;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int pair = blockIdx.x / P.splits, split = blockIdx.x % P.splits;
-  const int i_t = pair % P.n_t, i_c = pair / P.n_t;
+  const int i_t = blockIdx.x / P.splits, split = blockIdx.x % P.splits, i_c = blockIdx.y;
   const double chi = P.chi0 + i_c * P.dchi;
   const double T = exp(P.lnt0 + i_t * P.dlnt);
   ot_rates<NL, NS>(P, T, chi, base, coll);
@@ -519,14 +517,17 @@ __global__ __launch_bounds__(64) void ot_levels_kernel(const LevelsParams P) {
 // in the 256 registers of two wavefronts per SIMD; 63 levels would take 410.
 constexpr int kOtRows = 48;
 template <int NL>
-int launch_ot_reduce(const LevelsParams& P, int blocks, hipStream_t st) {
+int launch_ot_reduce(const LevelsParams& P, hipStream_t st) {
   constexpr int kStep = NL > 32 && NL <= kOtRows ? 4 : 8;
   if constexpr (NL > 8)
-    if (P.L <= NL - kStep) return launch_ot_reduce<NL - kStep>(P, blocks, st);
+    if (P.L <= NL - kStep) return launch_ot_reduce<NL - kStep>(P, st);
+  // A workgroup per (chi, T) and split, on two axes: a grid axis holds less than
+  // 2^32 threads, and there may be 2^24 pairs.
+  const dim3 blocks(P.n_t * P.splits, P.n_c);
   if constexpr (NL <= kOtRows)
-    hipLaunchKernelGGL((ot_reduce_rows_kernel<NL>), dim3(blocks), dim3(64 * kOtWaves), 0, st, P);
+    hipLaunchKernelGGL((ot_reduce_rows_kernel<NL>), blocks, dim3(64 * kOtWaves), 0, st, P);
   else
-    hipLaunchKernelGGL((ot_reduce_kernel<(NL < kMaxLevels ? NL : kMaxLevels)>), dim3(blocks),
+    hipLaunchKernelGGL((ot_reduce_kernel<(NL < kMaxLevels ? NL : kMaxLevels)>), blocks,
                        dim3(64 * kOtWaves), 0, st, P);
   return (int)hipGetLastError();
 }
@@ -826,7 +827,7 @@ iris_status iris_levels_create(const iris_molecule* mol, const iris_levels_confi
   const long pairs = (long)cfg->n_chi * cfg->n_t;
   P.splits = (int)std::max<long>(
       1, std::min<long>((cfg->n_n + iris::kOtWaves - 1) / iris::kOtWaves, 4096 / pairs));
-  e = iris::launch_ot_reduce<64>(P, (int)(pairs * P.splits), (hipStream_t)stream);
+  e = iris::launch_ot_reduce<64>(P, (hipStream_t)stream);
   if (!e) {
     const int blocks = (int)std::min<long>(n_pts, 2048);
     hipLaunchKernelGGL(iris::ot_levels_kernel, dim3(blocks), dim3(64), 0, (hipStream_t)stream, P);

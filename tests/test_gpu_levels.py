@@ -102,6 +102,26 @@ def test_grid_with_several_rounds_of_densities(tmp_path):
     lv.close()
 
 
+def test_grid_of_as_many_pairs_as_there_may_be():
+    # 4096 x 4096 (chi, T) pairs at one density: 2^32 threads in workgroups of 256.
+    path = os.path.join(GOLDEN, "toy3_lamda.dat")
+    mol = Lv.read_lamda(path)
+    n = 4096
+    cfg = dict(n_n=1, n_chi=n, n_t=n, ln_nh2_lo=5.0, ln_nh2_hi=5.0, chi_lo=0.3, chi_hi=1.0,
+               t_lo_k=4.0, t_hi_k=400.0)
+    say("[levels] 4096 x 4096 pairs")
+    lv = rt.Levels(rt.Molecule(path), 2, **cfg)
+    FU, FL = lv.grid()
+    lv.close()
+    chi = np.linspace(0.3, 1.0, n)
+    T = np.exp(np.linspace(math.log(4.0), math.log(400.0), n))
+    for ic, it in [(0, 0), (0, n - 1), (1234, 2345), (n - 1, 0), (n - 1, n - 1)]:
+        ref = oracle_grid(mol, dict(cfg, n_chi=1, n_t=1, chi_lo=chi[ic], chi_hi=chi[ic],
+                                    t_lo_k=T[it], t_hi_k=T[it]))
+        for a, b in ((FU[ic, it, 0], ref.FU.item()), (FL[ic, it, 0], ref.FL.item())):
+            assert abs(a - b) <= 2e-6 * abs(b), (ic, it)
+
+
 def test_grid_of_a_chain_that_cannot_be_reduced(tmp_path):
     # Nothing but spontaneous decay to a ground state listed last: the state
     # reduction has no way down from it, and the pivoting elimination answers.
