@@ -822,11 +822,17 @@ iris_status iris_levels_create(const iris_molecule* mol, const iris_levels_confi
   P.dlnt = cfg->n_t > 1 ? (std::log(cfg->t_hi_k) - std::log(cfg->t_lo_k)) / (cfg->n_t - 1) : 0.0;
   P.grid = lv->grid;
   P.unreduced = (int*)(base + oB);  // zeroed with the tables
-  // One workgroup per (chi, T), more where that leaves the GPU short of work
-  // (its densities then split over several, four nodes at least each).
+  // One workgroup per (chi, T), more where that leaves the GPU short of work: its
+  // densities then split over several, as many to each as it takes at once (four
+  // a wavefront up to kOtRows levels, one above), since each builds all the rates
+  // (128 x 8 x 12 nodes of 41 levels: 212 us at four a workgroup, 140 us at 16).
+  // Four a workgroup where every one still has a CU of its own (64 x 2 x 2 nodes
+  // of 48 levels: 133 against 135 us).
   const long pairs = (long)cfg->n_chi * cfg->n_t;
-  P.splits = (int)std::max<long>(
-      1, std::min<long>((cfg->n_n + iris::kOtWaves - 1) / iris::kOtWaves, 4096 / pairs));
+  const long quads = (cfg->n_n + 3) / 4;
+  const long parts = L > iris::kOtRows || pairs * quads <= 256 ? quads : (quads + 3) / 4;
+  static_assert(iris::kOtWaves == 4, "nodes of a workgroup");
+  P.splits = (int)std::max<long>(1, std::min<long>(parts, 4096 / pairs));
   e = iris::launch_ot_reduce<64>(P, (hipStream_t)stream);
   if (!e) {
     const int blocks = (int)std::min<long>(n_pts, 2048);

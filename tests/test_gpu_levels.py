@@ -102,6 +102,20 @@ def test_grid_with_several_rounds_of_densities(tmp_path):
     lv.close()
 
 
+@pytest.mark.parametrize("n_levels,n_n,n_chi,n_t", [(5, 37, 2, 3), (5, 37, 4, 30), (50, 37, 4, 30)])
+def test_grid_densities_split_over_workgroups(n_levels, n_n, n_chi, n_t, tmp_path):
+    # About four, sixteen and (one density a wavefront) four densities each, not
+    # all the same number.
+    path = str(tmp_path / "rotor.dat")
+    W.write_lamda(path, W.synthetic_rotor_molecule(n_levels=n_levels, seed=4))
+    cfg = dict(n_n=n_n, n_chi=n_chi, n_t=n_t, ln_nh2_lo=-2.0, ln_nh2_hi=16.0, chi_lo=0.3,
+               chi_hi=1.0, t_lo_k=4.0, t_hi_k=900.0)
+    say(f"[levels] {n_n} x {n_chi} x {n_t} grid of a rotor of {n_levels} levels")
+    lv = rt.Levels(rt.Molecule(path), 2, **cfg)
+    assert_grid_close(lv.grid(), oracle_grid(Lv.read_lamda(path), cfg, 2), "rotor")
+    lv.close()
+
+
 def test_grid_of_as_many_pairs_as_there_may_be():
     # 4096 x 4096 (chi, T) pairs at one density: 2^32 threads in workgroups of 256.
     path = os.path.join(GOLDEN, "toy3_lamda.dat")
