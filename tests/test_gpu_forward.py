@@ -384,3 +384,34 @@ def test_cold_cells(field, mode):
     for k in "TCDLB":
         e = M.err_inf(res[k].double().cpu().numpy(), ref[k])
         assert e <= TOL_FWD, (k, e)
+
+
+@pytest.mark.parametrize("axis,n", [(1, 8190), (0, 8200), (1, 8200), (2, 8200)])
+def test_fields_around_four_gigabytes(axis, n):
+    # FP64 fields just below and above 2^32 bytes, where the march's field
+    # offsets go from 32 to 64 bits: the last sightlines against the same ones
+    # in a cube of their own, bit for bit, with dust that cuts the march's chunks
+    # and under optically thin and selectively thin transfer.
+    shape = {0: (64, n, 1024), 1: (n, 64, 1024), 2: (n, 1024, 64)}[axis]
+    wide = 64 * n * 1024 * 8 >= 1 << 32
+    assert wide == (n == 8200)
+    last = {0: np.s_[:, -4:], 1: np.s_[-4:], 2: np.s_[-4:]}[axis]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(8)
+    small, big = [], []
+    for lo, hi in ((4.0, 9.0), (15.0, 80.0), (-6.0, 6.0), (1e-7, 3e-6)):
+        big.append(torch.full(shape, 0.5 * (lo + hi), device="cuda", dtype=torch.float64))
+        part = big[-1][last]
+        part.copy_(lo + (hi - lo) * torch.rand(part.shape, device="cuda", dtype=torch.float64,
+                                               generator=g))
+        small.append(part.contiguous())
+    for kw in (dict(), dict(kappa_dust_cm2g=3e4), dict(transfer="thin"), dict(transfer="selective")):
+        say(f"[fwd] {shape} along {axis}, {kw}")
+        args = dict(axis=axis, cell_cm=3e17, channels=rt.Channels(12, -6.0, 1.0),
+                    line=line_dict(**kw), components="TL")
+        a = rt.iris_rt_forward(*big, **args)
+        b = rt.iris_rt_forward(*small, **args)
+        torch.cuda.synchronize()
+        for k in "TL":
+            assert torch.equal(a[k][-4 * 1024:], b[k]), (kw, k)
+        del a, b
