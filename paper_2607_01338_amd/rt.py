@@ -227,13 +227,19 @@ def _check(status: int):
 
 # A small synthesis is bound by its host path, so the addresses go to C as plain
 # integers (every one lands in a c_void_p argument or field), and the stream of a
-# tensor's device is asked for without the Stream object around it (2.0 -> 0.1 us).
+# tensor's device is asked for without the Stream object around it (2.0 -> 0.1 us)
+# where this PyTorch has the private call for it.
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device) -> int:
-    return torch._C._cuda_getCurrentRawStream(device.index)
+    if _raw_stream is None or device.index is None:  # no index: the current device
+        return torch.cuda.current_stream(device).cuda_stream
+    return _raw_stream(device.index)
 
 
 def _empty_cubes(names, shape, device) -> dict:
@@ -620,9 +626,8 @@ class Levels:
         dev = torch.device(device) if device is not None else torch.device("cuda",
                                                                           torch.cuda.current_device())
         h = ctypes.c_void_p()
-        # The device may come without an index, and before any tensor is on it.
-        _check(lib.iris_levels_create(molecule.handle, ctypes.byref(cfg),
-                                      torch.cuda.current_stream(dev).cuda_stream,
+        torch.cuda.init()  # no tensor may be on the device yet
+        _check(lib.iris_levels_create(molecule.handle, ctypes.byref(cfg), _stream(dev),
                                       ctypes.byref(h)))
         self.handle = h
 

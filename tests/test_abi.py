@@ -458,3 +458,20 @@ def test_field_scan_needs_scratch_and_has_a_status_string():
     assert lib.iris_rt_check_fields(ctypes.byref(f), ctypes.c_void_p(0x1000), 256, None,
                                     None) == 1
     assert lib.iris_status_string(5) == b"non-finite or out-of-range field values"
+
+
+def test_stream_of_any_device(monkeypatch):
+    # The private call takes an index, and another PyTorch may not have it: the
+    # public one serves then.
+    import torch
+
+    class Stream:
+        cuda_stream = 77
+
+    asked = []
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda d: asked.append(d) or Stream())
+    monkeypatch.setattr(rt, "_raw_stream", lambda i: 100 + i)
+    assert rt._stream(torch.device("cuda", 3)) == 103 and not asked
+    assert rt._stream(torch.device("cuda")) == 77
+    monkeypatch.setattr(rt, "_raw_stream", None)
+    assert rt._stream(torch.device("cuda", 3)) == 77 and len(asked) == 2

@@ -8,6 +8,8 @@ data file is unpinned (the file is not available here)."""
 
 import math
 import os
+import subprocess
+import sys
 import time
 
 import numpy as np
@@ -409,3 +411,17 @@ def test_cmz_sightlines_with_the_paper_size_grid(rotor):
     ratio = float(res["L"].double().sum() / lte["L"].double().sum())
     say(f"      sum [L] OT / LTE = {ratio:.4f}")
     lv.close()
+
+
+def test_levels_before_any_tensor_and_without_a_device_index(rotor):
+    # In a fresh process: the device named with and without its index, PyTorch's
+    # CUDA state not yet set up.
+    code = """
+import sys
+from paper_2607_01338_amd import rt
+mol = rt.Molecule(sys.argv[1])
+grids = [rt.Levels(mol, 2, device=d, n_n=4, n_chi=2, n_t=3).grid() for d in ("cuda:0", "cuda")]
+assert (grids[0][0] == grids[1][0]).all() and (grids[0][0] > 0).all()
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    subprocess.run([sys.executable, "-c", code, rotor[0]], cwd=root, check=True, timeout=100)
