@@ -6,7 +6,8 @@
 // The beam is separable. Up to kBeamFusedRadius pixels one kernel does both
 // axes: it walks n1 row by row, convolves each row along n2 out of LDS and
 // keeps the 2R + 1 output rows it reaches in registers, so the cube is read
-// and written once. Wider beams, and an output that overlaps the cube, take
+// and written once. Wider beams, maps that leave it mostly halo (the rule is in
+// iris_beam_convolve), and an output that overlaps the cube, take
 // two passes, along n2 into a workspace and along n1 into the output: a lane
 // computes a run of four consecutive positions along the pass axis for four
 // channels (16-byte accesses when the rows allow it), so that the 2R + 1 taps
@@ -100,7 +101,7 @@ __global__ __launch_bounds__(256) void beam_pass_kernel(const BeamArgs a) {
 // 2R + 1 output rows in reach, held oldest first: the sum of row k moves down
 // to k - 1 in the multiply-add itself, so the window slides at no cost, and a
 // finished row leaves at the bottom. Positions outside the map count as zero.
-// Bound by HBM: 512 x 128 x 800, R = 5: two passes 320 us, this one 107 us
+// Bound by HBM: 512 x 128 x 800, R = 5: two passes 320 us, this one 95 us
 // (0.42 GB; the halos, (1 + 2R/64)(1 + 2R/segment), come from L2).
 constexpr int kBeamFusedRadius = 12;
 constexpr int kBeamCh = 32;     // channels of a workgroup
